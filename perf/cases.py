@@ -1,0 +1,510 @@
+"""Cases that time the geometry stage through its public entry points.
+
+A case is a dict of plain values.  "op" says which entry point one pass calls:
+
+  draw    one draw (GeometryStage.draw) into kept output buffers; a dynamic
+          draw either brings its plan ("plan": "kept") or has it built within
+          the call ("plan": "call", the first sight of an index buffer)
+  plan    dynamic batching alone (vr_plan_dynamic)
+  frame   many draws of uneven size as one captured frame (vr_frame_run)
+  walk    one step of the parallel random walk (vr_walk_step)
+  stream  a mesh pushed chunk by chunk through the streaming stage
+          (vr_stream_create .. vr_stream_finish)
+
+Meshes are those of paper_1805_08893_amd.workloads (jittered grids and
+subdivided icospheres in scan, Hilbert or random triangle order), built on
+the GPU so that preparing a case is quick.
+"""
+from __future__ import annotations
+
+import functools
+import math
+
+import numpy as np
+import torch
+
+from paper_1805_08893_amd import vr
+from paper_1805_08893_amd import workloads as W
+
+DEV = "cuda"
+SHADERS = {"mvp": W.SHADER_MVP, "phong": W.SHADER_PHONG, "offset": W.SHADER_OFFSET}
+
+
+# --------------------------------------------------------------------------
+# The cases
+# --------------------------------------------------------------------------
+def listed():
+    ico8 = {"op": "draw", "mesh": "ico", "level": 8, "order": "hilbert", "tris": 1310720, "shader": "phong", "amount": 8}
+    return [
+        # the smallest call: a small mesh seen for the first time, where launches and latency count
+        {"name": "small_grid_hash", "op": "draw", "mesh": "grid", "nx": 64, "ny": 64, "order": "scan", "tris": 7938,
+         "shader": "mvp", "amount": 0, "strategy": "dyn_hash", "batch": 341, "unique": 256, "plan": "call",
+         "outputs": "corners"},
+        # an ordinary mesh of odd sizes, streamed in static batches without any analysis of its indices
+        {"name": "odd_grid_static_hash", "op": "draw", "mesh": "grid", "nx": 317, "ny": 211, "order": "hilbert",
+         "tris": 100003, "shader": "phong", "amount": 4, "strategy": "static_hash", "batch": 85, "unique": 0,
+         "plan": "none", "outputs": "corners"},
+        # the scanned-model stand-in with no reuse, the baseline of every comparison
+        dict(ico8, name="ico8_naive", strategy="naive", batch=1, unique=0, plan="none", outputs="corners"),
+        # the same with wavefront ballot rounds
+        dict(ico8, name="ico8_ballot", strategy="static_ballot", batch=64, unique=0, plan="none", outputs="corners"),
+        # the same with sorting, the plan made at load time
+        dict(ico8, name="ico8_sort", strategy="dyn_sort", batch=341, unique=256, plan="kept", outputs="corners"),
+        # the same with hashing, an index buffer that changes from draw to draw: its plan is part of the call
+        dict(ico8, name="ico8_hash_planned", strategy="dyn_hash", batch=341, unique=256, plan="call",
+             outputs="corners"),
+        # the same with parallel hashing, for a consumer that takes shaded vertices and indices
+        dict(ico8, name="ico8_phash_indexed", strategy="dyn_phash", batch=341, unique=256, plan="kept",
+             outputs="indexed"),
+        # load-time analysis of a large mesh in an unoptimised order
+        {"name": "grid2048_random_plan", "op": "plan", "mesh": "grid", "nx": 2048, "ny": 2048, "order": "random",
+         "tris": 8380418, "batch": 341, "unique": 256},
+        # the largest draw: a fine patch with an expensive vertex program
+        {"name": "grid2048_offset_hash", "op": "draw", "mesh": "grid", "nx": 2048, "ny": 2048, "order": "hilbert",
+         "tris": 8380418, "shader": "offset", "amount": 64, "strategy": "dyn_hash", "batch": 341, "unique": 256,
+         "plan": "kept", "outputs": "corners"},
+        # a whole frame: thousands of draws of log-normal size, cheap programs without reuse, dear ones hashed
+        {"name": "scene_frame", "op": "frame", "draws": 2000, "median": 2440, "grid": 318, "level": 7, "batch": 128,
+         "unique": 128},
+        # one step of the random walk, agents sharing the search of their cell
+        {"name": "walk_hash", "op": "walk", "agents": 300000, "grid": 256, "radius": 16, "strategy": "static_hash",
+         "batch": 512},
+        # the streaming pipeline: chunks of a mesh consumed by triangle setup through a ring of two buffers
+        {"name": "stream_ballot", "op": "stream", "mesh": "ico", "level": 8, "order": "hilbert", "tris": 1310720,
+         "shader": "phong", "amount": 8, "strategy": "static_ballot", "batch": 64, "chunk": 65536, "slots": 2},
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _draw_mesh(rng, lo, hi, orders=("scan", "hilbert", "hilbert", "random")):
+    """A whole mesh or the prefix of one, lo..hi triangles."""
+    t = _log_int(rng, lo, hi)
+    order = rng.choice(orders)
+    if rng.random() < 0.5:
+        cells = t / 2 * rng.uniform(1.0, 1.5)
+        nx = max(3, int(math.sqrt(cells * rng.uniform(0.5, 2.0))) + 1)
+        ny = max(3, int(math.ceil(cells / (nx - 1))) + 1)
+        return {"mesh": "grid", "nx": nx, "ny": ny, "order": order, "tris": min(t, 2 * (nx - 1) * (ny - 1))}
+    level = 1
+    while 20 * 4 ** level < t:
+        level += 1
+    level = min(level, 8)
+    return {"mesh": "ico", "level": level, "order": order, "tris": min(t, 20 * 4 ** level)}
+
+
+def _draw_shader(rng):
+    kind = rng.choice(("mvp", "phong", "phong", "offset"))
+    return {"shader": kind, "amount": {"mvp": 0, "phong": rng.randint(1, 16), "offset": rng.choice((16, 33, 64))}[kind]}
+
+
+def draw(rng):
+    op = rng.choice(("draw",) * 6 + ("plan", "frame", "walk", "stream"))
+    if op == "draw":
+        strategy = rng.choice(("naive", "static_ballot", "static_sort", "static_hash", "dyn_sort", "dyn_hash", "dyn_hash",
+                               "dyn_phash", "dyn_ballot", "multi"))
+        case = {"op": op, **_draw_mesh(rng, 100, 3_000_000), **_draw_shader(rng), "strategy": strategy}
+        dynamic = strategy.startswith("dyn")
+        if strategy == "dyn_ballot":
+            case.update(batch=85, unique=64)
+        elif dynamic:
+            nu = rng.choice((64, 100, 128, 256, 256, 512))
+            case.update(batch=rng.choice((nu, nu * 4 // 3)), unique=nu)
+        elif strategy in ("naive", "multi"):
+            case.update(batch=1, unique=0)
+        else:
+            case.update(batch=rng.choice((32, 64, 85, 128, 171, 256)), unique=0)
+        case["plan"] = rng.choice(("kept", "call")) if dynamic else "none"
+        case["outputs"] = rng.choice(("corners", "corners", "indexed", "all"))
+        return case
+    if op == "plan":
+        nu = rng.choice((64, 128, 256, 256, 1024, 2048))
+        return {"op": op, **_draw_mesh(rng, 1000, 6_000_000), "batch": rng.choice((nu, nu * 4 // 3)), "unique": nu}
+    if op == "frame":
+        nu = rng.choice((128, 256))
+        return {"op": op, "draws": _log_int(rng, 16, 2000), "median": rng.randint(500, 2440), "grid": rng.randint(200, 318),
+                "level": rng.choice((6, 7)), "batch": nu, "unique": nu}
+    if op == "walk":
+        return {"op": op, "agents": _log_int(rng, 1000, 300_000), "grid": rng.choice((100, 200, 256)),
+                "radius": rng.randint(4, 16), "strategy": rng.choice(("naive", "static_hash")),
+                "batch": rng.choice((128, 256, 300, 512))}
+    mesh = _draw_mesh(rng, 20_000, 1_300_000, ("scan", "hilbert"))
+    return {"op": op, **mesh, **_draw_shader(rng), "strategy": rng.choice(("naive", "static_ballot", "static_hash")),
+            "batch": rng.choice((64, 85)), "chunk": min(65536, max(1000, mesh["tris"] // rng.randint(2, 20))),
+            "slots": rng.randint(2, 4)}
+
+
+# --------------------------------------------------------------------------
+# Meshes on the GPU
+# --------------------------------------------------------------------------
+def _generator(seed):
+    return torch.Generator(device=DEV).manual_seed(int(seed) & 0x7FFFFFFFFFFFFFFF)
+
+
+def _hilbert2d(x, y, bits):
+    x, y, d = x.clone(), y.clone(), torch.zeros_like(x)
+    n, s = 1 << bits, 1 << (bits - 1)
+    while s > 0:
+        rx, ry = ((x & s) > 0).long(), ((y & s) > 0).long()
+        d += s * s * ((3 * rx) ^ ry)
+        flip, swap = (ry == 0) & (rx == 1), ry == 0
+        x, y = torch.where(flip, n - 1 - x, x), torch.where(flip, n - 1 - y, y)
+        x, y = torch.where(swap, y, x), torch.where(swap, x, y)
+        s >>= 1
+    return d
+
+
+def _hilbert3d(q, bits):
+    """Transpose form of Skilling, "Programming the Hilbert curve" (2004)."""
+    x = [q[:, i].clone() for i in range(3)]
+    bit = 1 << (bits - 1)
+    while bit > 1:
+        p = bit - 1
+        for i in range(3):
+            hit = (x[i] & bit) != 0
+            t = torch.where(hit, torch.zeros_like(x[0]), (x[0] ^ x[i]) & p)
+            x[0] = torch.where(hit, x[0] ^ p, x[0]) ^ t
+            x[i] = x[i] ^ t if i else x[i]
+        bit >>= 1
+    x[1] = x[1] ^ x[0]
+    x[2] = x[2] ^ x[1]
+    t, bit = torch.zeros_like(x[0]), 1 << (bits - 1)
+    while bit > 1:
+        t = torch.where((x[2] & bit) != 0, t ^ (bit - 1), t)
+        bit >>= 1
+    key = torch.zeros_like(t)
+    for b in range(bits - 1, -1, -1):
+        for i in range(3):
+            key = (key << 1) | (((x[i] ^ t) >> b) & 1)
+    return key
+
+
+def _local_swaps(tris, gen):
+    """Swaps 5 % of the triangles with another one of their window of 256."""
+    full = len(tris) // 256 * 256
+    if not full:
+        return tris
+    at = torch.rand((full // 256, 256), generator=gen, device=DEV).argsort(1)[:, :26]
+    at = (at + 256 * torch.arange(full // 256, device=DEV)[:, None])
+    a, b = at[:, :13].reshape(-1), at[:, 13:].reshape(-1)
+    tris = tris.clone()
+    tris[a], tris[b] = tris[b], tris[a]
+    return tris
+
+
+def _grid(nx, ny, order, gen):
+    c = torch.arange((nx - 1) * (ny - 1), device=DEV)
+    ci, cj = c % (nx - 1), c // (nx - 1)
+    if order == "hilbert":
+        at = torch.argsort(_hilbert2d(ci, cj, max(1, (max(nx, ny) - 2).bit_length())), stable=True)
+        ci, cj = ci[at], cj[at]
+    v = cj * nx + ci
+    tris = torch.stack([v, v + 1, v + nx + 1, v, v + nx + 1, v + nx], 1).reshape(-1, 3)
+    u = torch.arange(nx * ny, device=DEV)
+    i, j = (u % nx).double(), (u // nx).double()
+    jit = torch.rand((nx * ny, 2), generator=gen, device=DEV, dtype=torch.float64) * 0.2 - 0.1
+    x, y = (i + jit[:, 0]) / (nx - 1), (j + jit[:, 1]) / (ny - 1)
+    ax, ay = 3 * math.pi * x, 2 * math.pi * y
+    nrm = torch.stack([-0.15 * math.pi * ax.cos() * ay.cos(), 0.1 * math.pi * ax.sin() * ay.sin(), torch.ones_like(x)], 1)
+    nrm = nrm / nrm.norm(dim=1, keepdim=True)
+    vert = torch.cat([torch.stack([x, y, 0.05 * ax.sin() * ay.cos()], 1), nrm, torch.stack([i / (nx - 1), j / (ny - 1)], 1)], 1)
+    return tris, vert, (0.5, 0.5, 0.0), 0.71
+
+
+def _ico(level, order, gen):
+    base = W.icosphere_mesh(0, 0)
+    pos = torch.from_numpy(base.vertices[:, :3].astype(np.float64)).to(DEV)
+    pos = pos / pos.norm(dim=1, keepdim=True)
+    f = torch.from_numpy(base.indices.reshape(-1, 3).astype(np.int64)).to(DEV)
+    for _ in range(level):
+        n, t = len(pos), len(f)
+        e = torch.cat([f[:, [0, 1]], f[:, [1, 2]], f[:, [2, 0]]]).sort(1).values
+        key, inv = torch.unique(e[:, 0] * n + e[:, 1], return_inverse=True)
+        mid = pos[key // n] + pos[key % n]
+        pos = torch.cat([pos, mid / mid.norm(dim=1, keepdim=True)])
+        ab, bc, ca = n + inv[:t], n + inv[t:2 * t], n + inv[2 * t:]
+        a, b, c = f[:, 0], f[:, 1], f[:, 2]
+        f = torch.stack([a, ab, ca, ab, b, bc, ca, bc, c, ab, bc, ca], 1).reshape(-1, 3)
+    if order == "hilbert":
+        q = ((pos[f].mean(1) + 1.0) * 512.0).floor().clamp(0, 1023).long()
+        f = f[torch.argsort(_hilbert3d(q, 10), stable=True)]
+    uv = torch.stack([torch.atan2(pos[:, 1], pos[:, 0]) / (2 * math.pi) + 0.5, pos[:, 2].clamp(-1, 1).acos() / math.pi], 1)
+    return f, torch.cat([pos, pos, uv], 1), (0.0, 0.0, 0.0), 1.0
+
+
+def _mesh(case, seed):
+    """(indices int32[3T], vertices float32[V, 8], centre, radius) of the case's mesh."""
+    gen = _generator(seed)
+    if case["mesh"] == "grid":
+        tris, vert, centre, radius = _grid(case["nx"], case["ny"], case["order"], gen)
+    else:
+        tris, vert, centre, radius = _ico(case["level"], case["order"], gen)
+    if case["order"] == "random":
+        tris = tris[torch.rand(len(tris), generator=gen, device=DEV, dtype=torch.float64).argsort()]
+    elif case["order"] == "hilbert":
+        tris = _local_swaps(tris, gen)
+    return tris[:case["tris"]].reshape(-1).to(torch.int32).contiguous(), vert.float().contiguous(), centre, radius
+
+
+def _params(case, seed, centre, radius):
+    kind = SHADERS[case["shader"]]
+    return W.make_shader(kind, seed % 65521, case["amount"] if kind == W.SHADER_PHONG else 0,
+                         case["amount"] if kind == W.SHADER_OFFSET else 0, centre, radius)
+
+
+# --------------------------------------------------------------------------
+# Prepare and run
+# --------------------------------------------------------------------------
+@functools.lru_cache(maxsize=1)
+def _stage():
+    """A program keeps one context."""
+    return vr.GeometryStage(0)
+
+
+def _plan(stage, idx, num_verts, case):
+    plan = torch.zeros(idx.numel() // 3 + 2, dtype=torch.int32, device=DEV)
+    stage.check(vr.vr_plan_dynamic(stage.ctx, idx, num_verts, case["unique"], case["batch"], plan))
+    return plan
+
+
+def _prepare_draw(case, seed):
+    stage = _stage()
+    idx, vtx, centre, radius = _mesh(case, seed)
+    sp = _params(case, seed, centre, radius)
+    strategy, want = vr.STRATEGIES[case["strategy"]], case["outputs"]
+    res = stage.alloc_outputs(case["tris"], strategy, case["batch"], corners=want != "indexed", tris=want != "corners",
+                              verts=want != "corners", local_idx=want == "all" and strategy != vr.VR_MULTI,
+                              units=want == "all", num_vertices=len(vtx))
+    for t in res.values():
+        t.zero_()
+    plan = _plan(stage, idx, len(vtx), case) if case["plan"] == "kept" else None
+    return {"stage": stage, "idx": idx, "vtx": vtx, "shader": vr.make_shader(sp), "strategy": strategy,
+            "batch": case["batch"], "opts": vr.make_opts(max_unique=case["unique"], plan=plan), "plan": plan, "res": res}
+
+
+def _run_draw(s):
+    return s["stage"].draw(s["idx"], s["vtx"], s["shader"], s["strategy"], s["batch"], s["opts"], s["res"])
+
+
+def _prepare_plan(case, seed):
+    idx, vtx, _, _ = _mesh(case, seed)
+    return {"stage": _stage(), "idx": idx, "verts": len(vtx), "unique": case["unique"], "batch": case["batch"],
+            "plan": torch.zeros(idx.numel() // 3 + 2, dtype=torch.int32, device=DEV)}
+
+
+def _run_plan(s):
+    s["stage"].check(vr.vr_plan_dynamic(s["stage"].ctx, s["idx"], s["verts"], s["unique"], s["batch"], s["plan"]))
+    return s["plan"]
+
+
+def _frame_bases(case):
+    """Grids and icospheres in Hilbert and in scan order; a draw is the prefix of one."""
+    return [{"mesh": "grid", "nx": case["grid"], "ny": case["grid"], "order": o, "tris": 2 * (case["grid"] - 1) ** 2}
+            for o in ("hilbert", "scan")] + [{"mesh": "ico", "level": case["level"], "order": o,
+                                              "tris": 20 * 4 ** case["level"]} for o in ("hilbert", "scan")]
+
+
+def _frame_draws(case):
+    """(base, triangles, program) of every draw: the same for every seed."""
+    rng, bases = np.random.default_rng(3), _frame_bases(case)
+    sizes = np.clip(np.exp(rng.normal(math.log(case["median"]), 1.2, case["draws"])), 100, 200_000).astype(int)
+    base, prog = rng.integers(0, len(bases), case["draws"]), rng.integers(0, 3, case["draws"])
+    return [(int(b), int(min(t, bases[b]["tris"])), int(p)) for b, t, p in zip(base, sizes, prog)]
+
+
+FRAME_PROGRAMS = ({"shader": "mvp", "amount": 0}, {"shader": "phong", "amount": 4}, {"shader": "phong", "amount": 16})
+
+
+def _prepare_frame(case, seed):
+    stage, bases, draws = _stage(), _frame_bases(case), _frame_draws(case)
+    meshes = [_mesh(b, seed + 7 * k) for k, b in enumerate(bases)]
+    params = [[_params(p, seed + k, m[2], m[3]) for p in FRAME_PROGRAMS] for k, m in enumerate(meshes)]
+    plans = [_plan(stage, m[0], len(m[1]), case) for m in meshes]
+    total = sum(t for _, t, _ in draws)
+    corners = torch.zeros((3 * total, vr.OUT_FLOATS), dtype=torch.float32, device=DEV)
+    counters = torch.zeros((len(draws), 4), dtype=torch.int64, device=DEV)
+    table, at = [], 0
+    for d, (b, t, p) in enumerate(draws):
+        idx, vtx = meshes[b][0][:3 * t], meshes[b][1]
+        how = (vr.VR_DYN_HASH, case["batch"]) if p == 2 else (vr.VR_NAIVE, 1)
+        table.append(vr.make_draw(idx, vtx, 3 * b + p, *how, corners[3 * at:3 * (at + t)], counters[d],
+                                  case["unique"] if p == 2 else 0, plans[b] if p == 2 else None))
+        at += t
+    rc, frame = vr.vr_frame_create(stage.ctx, table, [s for row in params for s in row], capture_graph=True)
+    stage.check(rc)
+    return {"stage": stage, "frame": _Frame(frame), "corners": corners, "counters": counters, "meshes": meshes,
+            "plans": plans}
+
+
+class _Frame:
+    def __init__(self, handle):
+        self.handle = handle
+
+    def __del__(self):
+        vr.vr_frame_destroy(self.handle)
+
+
+def _run_frame(s):
+    s["stage"].check(vr.vr_frame_run(s["frame"].handle))
+    return {"corners": s["corners"], "counters": s["counters"]}
+
+
+def _prepare_walk(case, seed):
+    w = W.walk_setup(seed=seed % 65521, grid=case["grid"], agents=case["agents"], radius=case["radius"])
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a.view(np.int32) if a.dtype == np.uint32 else a)).to(DEV)  # noqa: E731
+    keys = dev(w.keys)
+    return {"stage": _stage(), "keys": keys, "activity": dev(w.activity), "grid": w.grid, "moves": dev(w.moves),
+            "weights": dev(w.weights), "uniforms": dev(W.walk_uniforms(seed % 65521, 0, case["agents"])),
+            "strategy": vr.STRATEGIES[case["strategy"]], "batch": case["batch"], "next": torch.zeros_like(keys),
+            "counters": torch.zeros(4, dtype=torch.int64, device=DEV)}
+
+
+def _run_walk(s):
+    s["stage"].check(vr.vr_walk_step(s["stage"].ctx, s["keys"], s["activity"], s["grid"], s["moves"], s["weights"],
+                                     s["uniforms"], s["strategy"], s["batch"], s["next"], s["counters"]))
+    return {"keys": s["next"], "counters": s["counters"]}
+
+
+def _prepare_stream(case, seed):
+    idx, vtx, centre, radius = _mesh(case, seed)
+    chunks = [idx[3 * t:3 * min(t + case["chunk"], case["tris"])] for t in range(0, case["tris"], case["chunk"])]
+    return {"stage": _stage(), "chunks": chunks, "vtx": vtx, "shader": vr.make_shader(_params(case, seed, centre, radius)),
+            "strategy": vr.STRATEGIES[case["strategy"]], "batch": case["batch"], "slots": case["slots"],
+            "chunk": case["chunk"], "records": torch.zeros((case["tris"], 8), dtype=torch.float32, device=DEV)}
+
+
+def _run_stream(s):
+    check = s["stage"].check
+    st, h = vr.vr_stream_create(s["stage"].ctx, s["slots"], s["chunk"], 1920, 1080, s["records"])
+    check(st)
+    try:
+        for c in s["chunks"]:
+            check(vr.vr_stream_push(h, c, s["vtx"], s["shader"], s["strategy"], s["batch"]))
+        st, tris, visible, invocations = vr.vr_stream_finish(h)
+        check(st)
+    finally:
+        vr.vr_stream_destroy(h)
+    return {"records": s["records"], "totals": [tris, visible, invocations]}
+
+
+_PREPARE = {"draw": _prepare_draw, "plan": _prepare_plan, "frame": _prepare_frame, "walk": _prepare_walk,
+            "stream": _prepare_stream}
+_RUN = {"draw": _run_draw, "plan": _run_plan, "frame": _run_frame, "walk": _run_walk, "stream": _run_stream}
+
+
+def prepare(case, seed):
+    return {"op": case["op"], "state": _PREPARE[case["op"]](case, int(seed))}
+
+
+def run(state):
+    return _RUN[state["op"]](state["state"])
+
+
+# --------------------------------------------------------------------------
+# What a pass cannot do without
+# --------------------------------------------------------------------------
+def _num_verts(case):
+    return case["nx"] * case["ny"] if case["mesh"] == "grid" else 10 * 4 ** case["level"] + 2
+
+
+def _referenced(case):
+    """Vertices the triangles refer to: about half as many as triangles in an
+    ordered prefix, nearly all within reach in a random one."""
+    v, t = _num_verts(case), case["tris"]
+    return v * (1 - math.exp(-3 * t / v)) if case["order"] == "random" else min(v, t / 2 + math.sqrt(2 * t))
+
+
+def _vertex_flops(case):
+    return {"mvp": 49, "phong": 80 + 48 * case["amount"], "offset": 60 + 9 * case["amount"]}[case["shader"]]
+
+
+def work(case):
+    if case["op"] == "frame":
+        bases, n_bytes, flops = _frame_bases(case), 0.0, 0.0
+        for b, t, p in _frame_draws(case):
+            part = dict(bases[b], tris=t)
+            n_bytes += 156 * t + 32 * _referenced(part)
+            flops += _vertex_flops(FRAME_PROGRAMS[p]) * (_referenced(part) if p == 2 else 3 * t)
+        return {"bytes": n_bytes, "flops": flops}
+    if case["op"] == "walk":
+        n, cells, moves = case["agents"], case["grid"] ** 2, math.pi * case["radius"] ** 2
+        searched = min(n, cells) if case["strategy"] == "static_hash" else n
+        return {"bytes": 12 * n + 4 * cells + 6 * moves, "flops": searched * moves}
+    t, u = case["tris"], _referenced(case)
+    if case["op"] == "plan":
+        return {"bytes": 12 * t + 4 * (t / case["batch"] + 2), "flops": 0}
+    naive = case["strategy"] == "naive"
+    if case["op"] == "stream":
+        return {"bytes": 12 * t + 32 * u + 32 * t, "flops": _vertex_flops(case) * (3 * t if naive else u)}
+    shaded = 3 * t if naive else _num_verts(case) if case["strategy"] == "multi" else u
+    out = {"corners": 144 * t, "indexed": 12 * t + 48 * shaded, "all": 144 * t + 12 * t + 6 * t + 48 * shaded}
+    return {"bytes": 12 * t + 32 * u + out[case["outputs"]], "flops": _vertex_flops(case) * shaded}
+
+
+# --------------------------------------------------------------------------
+# The vertex programs in 64 bits
+# --------------------------------------------------------------------------
+def _shade64(vtx, sp):
+    f = lambda a: torch.from_numpy(np.asarray(a, dtype=np.float64)).to(DEV)  # noqa: E731
+    unit = lambda v: v / v.norm(dim=1, keepdim=True)  # noqa: E731
+    v = vtx.double()
+    pos, nrm = v[:, :3], v[:, 3:6]
+    if sp.kind == W.SHADER_OFFSET:
+        c = [float(x) for x in sp.coef]
+        ph, h = pos @ f(c[4:7]), torch.zeros_like(pos[:, 0])
+        for _ in range(sp.iterations):
+            h = h + c[0] * (((c[3] * h + c[2]) * h + c[1]) * h + ph - h)
+        pos = pos + h[:, None] * nrm
+    mvp, model = f(sp.mvp).reshape(4, 4), f(sp.model).reshape(3, 4)
+    clip, n = pos @ mvp[:, :3].T + mvp[:, 3], unit(nrm @ f(sp.normal).reshape(3, 3).T)
+    rgb = f(sp.ambient).expand(len(v), 3).clone()
+    if sp.kind == W.SHADER_PHONG:
+        w = pos @ model[:, :3].T + model[:, 3]
+        view = unit(f(sp.eye) - w)
+        kd, ks, katt = (float(np.float32(x)) for x in (sp.kd, sp.ks, sp.katt))
+        for k in range(sp.num_lights):
+            d = f(sp.lights[k, :3]) - w
+            d2 = (d * d).sum(1)
+            ld = d / d2.sqrt()[:, None]
+            ndl = (n * ld).sum(1)
+            refl = 2 * ndl[:, None] * n - ld
+            spec = (refl * view).sum(1).clamp(min=0) ** (2 ** sp.spec_squarings)
+            rgb += ((kd * ndl.clamp(min=0) + ks * spec) / (1 + katt * d2))[:, None] * f(sp.lights[k, 3:])
+    return torch.cat([clip, n, v[:, 6:8], rgb], 1)
+
+
+def exact(case, seed):
+    seed = int(seed)
+    if case["op"] == "draw":
+        idx, vtx, centre, radius = _mesh(case, seed)
+        shaded = _shade64(vtx, _params(case, seed, centre, radius))
+        want, out = case["outputs"], {}
+        if want != "indexed":
+            out["corners"] = shaded[idx.long()]
+        if want != "corners" and case["strategy"] == "naive":
+            out["verts"] = shaded[idx.long()]
+        if want != "corners" and case["strategy"] == "multi":
+            rows = max(3 * case["tris"], len(vtx))
+            out["verts"] = torch.cat([shaded, shaded.new_zeros((rows - len(vtx), vr.OUT_FLOATS))])
+        return out or None
+    if case["op"] == "frame":
+        meshes = [_mesh(b, seed + 7 * k) for k, b in enumerate(_frame_bases(case))]
+        shaded = [[_shade64(m[1], _params(p, seed + k, m[2], m[3])) for p in FRAME_PROGRAMS] for k, m in enumerate(meshes)]
+        return {"corners": torch.cat([shaded[b][p][meshes[b][0][:3 * t].long()] for b, t, p in _frame_draws(case)])}
+    if case["op"] == "stream":
+        idx, vtx, centre, radius = _mesh(case, seed)
+        c = _shade64(vtx, _params(case, seed, centre, radius))[idx.long(), :4].reshape(-1, 3, 4)
+        size = c.new_tensor([1920.0, 1080.0])
+        s = (c[..., :2] / c[..., 3:] + 1) * (size / 2)
+        lo, hi = s.amin(1).clamp(min=0), torch.minimum(s.amax(1), size)
+        e, g = s[:, 1] - s[:, 0], s[:, 2] - s[:, 0]
+        area = e[:, 0] * g[:, 1] - g[:, 0] * e[:, 1]
+        seen = (area > 0) & (lo < hi).all(1)
+        zero = torch.zeros_like(area)
+        # the visibility flag is a whole number (1) in a float's place
+        flag = torch.where(seen, torch.full_like(zero, float(np.uint32(1).view(np.float32))), zero)
+        front = (c[..., 3] > 0).all(1)
+        return {"records": torch.cat([lo, hi, torch.stack([area, flag, zero, zero], 1)], 1) * front[:, None]}
+    return None   # plans and walks are whole numbers
