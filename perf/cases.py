@@ -120,8 +120,11 @@ def draw(rng):
         case["outputs"] = rng.choice(("corners", "corners", "indexed", "all"))
         return case
     if op == "plan":
-        nu = rng.choice((64, 128, 256, 256, 1024, 2048))
-        return {"op": op, **_draw_mesh(rng, 1000, 6_000_000), "batch": rng.choice((nu, nu * 4 // 3)), "unique": nu}
+        # budgets that bind, so that the plan depends on the indices
+        mesh = _draw_mesh(rng, 1000, 6_000_000, ("hilbert", "random"))
+        nu = rng.choice([n for n in (64, 128, 256, 256, 1024, 2048) if n == 64 or 16 * n <= mesh["tris"]])
+        return {"op": op, **mesh, "batch": nu * 4 // 3 if mesh["order"] == "random" and rng.random() < 0.5 else 2 * nu,
+                "unique": nu}
     if op == "frame":
         nu = rng.choice((128, 256))
         return {"op": op, "draws": _log_int(rng, 16, 2000), "median": rng.randint(500, 2440), "grid": rng.randint(200, 318),
