@@ -38,15 +38,11 @@ struct FrameVariant {
     uint32_t occ;   // hashing variant held to eight wavefronts per SIMD (its LDS allows them)
 };
 
+// A frame's draw: its arguments as a single draw has them (corners only; the
+// aggregates' place is the frame's), and what the frame needs besides.
 struct DrawDesc {
-    const uint32_t *idx;
-    const f4 *vtx;
-    f4 *corners;
-    unsigned long long *counters;
-    const uint32_t *plan;
-    uint32_t V, T, batch_tris, num_batches;
+    DrawArgs A;
     uint32_t shader, mode, kind;
-    uint32_t max_idx, max_uniq, hash_bits, probes;
     uint32_t slot_cap;   // aggregate slots the host reserved for the draw's batches
 };
 
@@ -72,10 +68,10 @@ __device__ __forceinline__ uint32_t plan_prefix_batches(const uint32_t *plan, ui
 __device__ __forceinline__ void frame_draw_units(const DrawDesc &D, uint32_t &units, uint32_t &slots,
                                                  uint32_t *err) {
     if (D.mode == kFrameNaive) {
-        units = slots = (uint32_t)((3ull * D.T + 255) / 256);
+        units = slots = (uint32_t)((3ull * D.A.T + 255) / 256);
         return;
     }
-    uint32_t nb = D.T == 0 ? 0u : (D.plan ? plan_prefix_batches(D.plan, D.T) : D.num_batches);
+    uint32_t nb = D.A.T == 0 ? 0u : (D.A.plan ? plan_prefix_batches(D.A.plan, D.A.T) : D.A.num_batches);
     if (nb > D.slot_cap) {
         raise_error(err, VR_ERR_CAPACITY);
         nb = D.slot_cap;
@@ -121,47 +117,27 @@ __global__ __launch_bounds__(1024) void k_frame_prepare(const DrawDesc *draws, c
     }
 }
 
-__device__ __forceinline__ DrawArgs frame_args(const DrawDesc &D, unsigned long long *agg, uint32_t *err,
-                                               unsigned long long *total_inv) {
-    DrawArgs A{};
-    A.idx = D.idx;
-    A.vtx = D.vtx;
-    A.V = D.V;
-    A.T = D.T;
-    A.batch_tris = D.batch_tris;
-    A.num_batches = D.num_batches;
-    A.plan = D.plan;
-    A.corners = D.corners;
-    A.agg = agg;
-    A.err = err;
-    A.total_inv = total_inv;
-    A.hash_bits = D.hash_bits;
-    A.probes = D.probes;
-    A.max_idx = D.max_idx;
-    A.max_uniq = D.max_uniq;
-    A.need_prefix = 0;
-    A.status_cap = 0xFFFFFFFFu;
-    return A;
-}
-
 template <int MODE, int KIND>
-__device__ __forceinline__ void frame_unit(const DrawArgs &A, const vr_shader_params &sh, uint32_t local,
-                                           uint32_t nb, unsigned char *smem, uint32_t ballot_stride) {
+__device__ __forceinline__ void frame_unit(ArgsPtr args, ShaderPtr shader, uint32_t local, uint32_t nb,
+                                           unsigned char *smem, uint32_t ballot_stride,
+                                           unsigned long long *agg) {
+    const DrawArgs &A = *(const DrawArgs *)args;
+    const vr_shader_params &sh = *(const vr_shader_params *)shader;
     if (MODE == kFrameSort) {
-        dedup_unit<kFrameNT, kSort, KIND>(A, sh, local, nb, smem);
+        dedup_unit<kFrameNT, kSort, KIND, false, 8>(args, shader, local, nb, smem, agg);
     } else if (MODE == kFrameHash) {
-        dedup_unit<kFrameNT, kHash, KIND>(A, sh, local, nb, smem);
+        dedup_unit<kFrameNT, kHash, KIND, false, 8>(args, shader, local, nb, smem, agg);
     } else if (MODE == kFramePHash) {
-        dedup_unit<kFrameNT, kPHash, KIND>(A, sh, local, nb, smem);
+        dedup_unit<kFrameNT, kPHash, KIND, false, 8>(args, shader, local, nb, smem, agg);
     } else if (MODE == kFrameBallot) {
         const uint32_t w = threadIdx.x / kWave;
         const uint32_t b = 4 * local + w;
         unsigned char *mine = smem + w * ballot_stride;
-        if (b < nb) ballot_batch<KIND>(A, sh, b, nb, mine);
+        if (b < nb) ballot_batch<KIND>(A, sh, b, nb, mine, agg);
         __syncthreads();
     } else {
-        const unsigned long long agg = naive_chunk<KIND>(A, sh, local, (f4 *)smem);
-        if (threadIdx.x == 0) A.agg[local] = agg;
+        const unsigned long long sum = naive_chunk<KIND>(A, sh, local, (f4 *)smem);
+        if (threadIdx.x == 0) agg[local] = sum;
     }
 }
 
@@ -180,8 +156,7 @@ __global__ __launch_bounds__(kFrameNT) __attribute__((amdgpu_waves_per_eu(OCC ? 
                                                     const uint32_t *__restrict__ unit_base,
                                                     const uint32_t *__restrict__ slot_base,
                                                     unsigned long long *agg, uint32_t unit_lds,
-                                                    uint32_t ballot_stride, uint32_t *err,
-                                                    unsigned long long *total_inv) {
+                                                    uint32_t ballot_stride) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const uint32_t m = hi - lo;
     uint32_t *s_base = (uint32_t *)(smem + unit_lds);
@@ -191,8 +166,9 @@ __global__ __launch_bounds__(kFrameNT) __attribute__((amdgpu_waves_per_eu(OCC ? 
     const uint32_t G = gridDim.x;
     constexpr uint32_t kChunk = frame_chunk(MODE);
     uint32_t kd = 0xFFFFFFFFu;   // the draw whose descriptor is loaded
-    DrawArgs A{};
-    const vr_shader_params *sh = shaders;
+    ArgsPtr args = nullptr;
+    ShaderPtr sh = nullptr;
+    unsigned long long *mine = agg;
     uint32_t nb = 0;
     // The draw index and everything loaded through it are the same in every
     // lane; reading the LDS bases through readfirstlane lets the compiler see
@@ -213,12 +189,13 @@ __global__ __launch_bounds__(kFrameNT) __attribute__((amdgpu_waves_per_eu(OCC ? 
             while (u >= base_at(k + 1)) ++k;   // units of empty draws are skipped
             if (k != kd) {   // descriptors are loaded once per draw, not per unit
                 kd = k;
-                const DrawDesc D = draws[order[lo + k]];
-                A = frame_args(D, agg + slot_base[lo + k], err, total_inv);
-                sh = shaders + D.shader;
+                const VR_CONSTANT DrawDesc *D = (const VR_CONSTANT DrawDesc *)(uint64_t)(draws + order[lo + k]);
+                args = &D->A;
+                mine = agg + slot_base[lo + k];
+                sh = (ShaderPtr)(uint64_t)(shaders + D->shader);
                 nb = slot_base[lo + k + 1] - slot_base[lo + k];
             }
-            frame_unit<MODE, KIND>(A, *sh, u - base_at(k), nb, smem, ballot_stride);
+            frame_unit<MODE, KIND>(args, sh, u - base_at(k), nb, smem, ballot_stride, mine);
         }
     }
 }
@@ -242,7 +219,7 @@ __global__ __launch_bounds__(1024) void k_frame_finish(const DrawDesc *draws, co
     for (int s = 32; s > 0; s >>= 1) sum += __shfl_xor(sum, s, kWave);
     if (lane_id() == 0) {
         const unsigned long long inv = sum & 0xFFFFFFFFull, units = sum >> 32;
-        unsigned long long *c = draws[order[d]].counters;
+        unsigned long long *c = draws[order[d]].A.counters;
         if (c) {
             c[0] = inv;
             c[1] = units;

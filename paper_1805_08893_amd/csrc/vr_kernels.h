@@ -2,6 +2,8 @@
 // deduplication over static or dynamic batches, and wave64 ballot rounds.
 #pragma once
 
+#include <type_traits>
+
 #include "vr_device.h"
 
 namespace vr {
@@ -37,6 +39,23 @@ struct DrawArgs {
     uint32_t status_cap;        // look-back words available
     uint32_t stream_verts;      // no corners: shaded vertices stream out through an NT-row stage
 };
+
+// Draw arguments and shader parameters in constant memory (a launch's kernel
+// arguments, a frame's tables): read with scalar loads where they are used.
+#define VR_CONSTANT __attribute__((address_space(4)))
+using ArgsPtr = const VR_CONSTANT DrawArgs *;
+using ShaderPtr = const VR_CONSTANT vr_shader_params *;
+
+// The same pointer, of unknown origin to the compiler: what is read through
+// it is read again instead of being kept from before.  A unit's phases use
+// different fields, and kept across them they exceed the scalar registers and
+// are spilled into vector lanes, two vector instructions for each.
+template <typename T>
+__device__ __forceinline__ const VR_CONSTANT T *reread(const VR_CONSTANT T *p) {
+    uint64_t a = (uint64_t)p;
+    asm volatile("" : "+s"(a));
+    return (const VR_CONSTANT T *)a;
+}
 
 // Units a launch may take: the plan's count, bounded by the look-back
 // capacity (a plan built for other limits raises an error instead of
@@ -122,12 +141,12 @@ __device__ __forceinline__ void shade_to_lds(const DrawArgs &A, const vr_shader_
 // Assembly (Section 4.2): every corner of the unit's triangles receives its
 // shaded vertex.  The unit's corner rows are one contiguous span, so lane q
 // stores float4 q of the span: fully coalesced 16-byte stores.
-template <int NT, typename LocalT>
+template <int NT, bool FULL, typename LocalT>
 __device__ __forceinline__ void write_unit(const DrawArgs &A, uint32_t t0, uint32_t ntri, const LocalT *s_local,
                                            const f4 *s_sv, uint32_t inv, uint32_t vbase, uint32_t unit,
                                            uint32_t tid, bool verts_written = false) {
     const uint32_t ncorner = 3 * ntri;
-    if (A.corners) {
+    if (!FULL || A.corners) {
         // float4 q of the span is part q % 3 of corner q / 3.  Lane tid takes
         // q = tid + NT i; NT is a power of two, so NT = r (mod 3) with r = 1
         // or 2, and for i = 3 m + j the corner is NT m + kj[j] and the part
@@ -157,6 +176,7 @@ __device__ __forceinline__ void write_unit(const DrawArgs &A, uint32_t t0, uint3
                 if (q + j * NT < cnt) __builtin_nontemporal_store(row[j], dst + q + j * NT);
         }
     }
+    if (!FULL) return;
     if (A.tris || A.local_idx) {
         for (uint32_t k = tid; k < ncorner; k += NT) {
             const uint32_t l = s_local[k];
@@ -322,87 +342,69 @@ __global__ __launch_bounds__(256) void k_multi_assemble(DrawArgs A, const f4 *sh
 // LDS layout of the dedup kernel (bytes), shared with the host launcher.
 // ---------------------------------------------------------------------------
 struct DedupLds {
-    uint32_t keys, local, pairs, stab, table, first, uniq, sv, tmp, total;
+    uint32_t local, pairs, stab, table, first, uniq, sv, tmp, total;
 };
 
 __host__ __device__ inline uint32_t align16(uint32_t x) { return (x + 15u) & ~15u; }
 
-__host__ __device__ inline uint32_t pow2_ceil(uint32_t x) {
-    uint32_t p = 1;
-    while (p < x) p <<= 1;
-    return p;
-}
+// Corners a thread keeps in registers during deduplication; a unit of more
+// than kRows * NT corners is deduplicated in chunks of that many.
+constexpr uint32_t kRows = 4;
 
 // Count groups per digit of the sort's radix passes: rounds x wavefronts,
 // padded to whole words.
-__host__ __device__ inline uint32_t sort_groups(uint32_t max_idx, uint32_t nt) {
-    const uint32_t g = (max_idx + nt - 1) / nt * (nt / 64);
+__host__ __device__ inline uint32_t sort_groups(uint32_t max_keys, uint32_t nt) {
+    const uint32_t g = (max_keys + nt - 1) / nt * (nt / 64);
     return (g + 3u) & ~3u;
 }
 
 // The local ids and the unique list live from deduplication to the end of
 // the unit; the shaded vertices (written after deduplication) share their
-// region with what deduplication alone uses: the indices, then the sort's
-// two position buffers and its per-digit counts (uint8) and offsets
-// (uint16), or the hash table and the first-position words.  sv_rows shaded vertices are
-// kept: every unique vertex of a unit when corners are assembled, else one
-// stage of nt rows through which the shaded vertices stream out.
-__host__ __device__ inline DedupLds dedup_lds_layout(int mode, uint32_t max_idx, uint32_t max_uniq,
+// region with what deduplication alone uses: the hash table and each slot's
+// id word (or a static sort's indices), then the sort's two position buffers
+// and its per-digit counts (uint8) and offsets (uint16).  sv_rows shaded vertices are kept: every
+// unique vertex of a unit when corners are assembled, else one stage of nt
+// rows through which the shaded vertices stream out.
+__host__ __device__ inline DedupLds dedup_lds_layout(int mode, bool dynamic, uint32_t max_idx, uint32_t max_uniq,
                                                      uint32_t hash_bits, uint32_t nt, uint32_t sv_rows) {
     DedupLds L{};
     uint32_t off = 0;
-    if (mode == kSort) {
-        // The sort writes the local ids and the unique list only after its
-        // last pass, so they sit in the space of its count tables, past the
-        // buffers the run-end scan still reads and past the shaded vertices
-        // (written from the start once the sort's buffers are dead).
-        uint32_t d = 0;
-        L.keys = d;  d += align16(4 * max_idx);
-        L.pairs = d; d += align16(4 * max_idx);   // two uint16 position buffers
-        L.stab = d;  d += 3u * 256u * sort_groups(max_idx, nt);
-        L.sv = 0;
-        uint32_t lu = max(align16(48 * sv_rows), L.stab);
-        L.local = lu; lu += align16(2 * max_idx);   // uint16 ids < max_idx
-        L.uniq = lu;  lu += align16(4 * max_uniq);
-        L.table = L.first = 0;
-        off = max(lu, d);
+    L.local = off; off += align16(2 * max_idx);   // uint16: hash slots < 8192, then ids < max_idx
+    L.uniq = off;  off += align16(4 * max_uniq);
+    L.sv = off;
+    uint32_t d = off;
+    L.table = d;
+    if (mode == kSort && !dynamic) {
+        d += align16(4 * max_idx);   // every index, as no table drops duplicates
     } else {
-        L.local = off; off += align16(2 * max_idx);   // uint16: hash slots < 8192, then ids < max_idx
-        L.uniq = off;  off += align16(4 * max_uniq);
-        L.sv = off;
-        uint32_t d = off;
-        L.keys = d;    d += align16(4 * max_idx);
-        L.pairs = L.stab = 0;
-        L.table = d; d += align16(4u << hash_bits);
+        d += align16(4u << hash_bits);
         L.first = d; d += align16(4u << hash_bits);
-        off = max(align16(off + 48 * sv_rows), align16(d));
     }
-    L.tmp = off;  off += 64;
+    if (mode == kSort) {   // of the indices that are sorted: all, or the distinct ones
+        const uint32_t m = dynamic ? max_uniq : max_idx;
+        L.pairs = d; d += align16(4 * m);   // two uint16 position buffers
+        L.stab = d;  d += 3u * 256u * sort_groups(m, nt);
+    }
+    off = max(align16(off + 48 * sv_rows), align16(d));
+    L.tmp = off;  off += 64;   // scan words, or counts (uint8) per row and wavefront
     L.total = off;
     return L;
 }
 
-// Ranks flagged entries of a unit in index order with a blocked scan:
-// thread t owns entries [t*E, t*E+E).  flag(i) is evaluated once and kept
-// in a register mask (E <= 32).  Returns the number of flagged entries.
-template <int NT, typename FlagF, typename EmitF>
-__device__ __forceinline__ uint32_t rank_flagged(uint32_t n, uint32_t *s_tmp, FlagF flag, EmitF emit) {
-    const uint32_t E = (n + NT - 1) / NT;
-    const uint32_t lo = min(n, threadIdx.x * E), hi = min(n, lo + E);
-    uint32_t mask = 0, cnt = 0;
-    for (uint32_t i = lo; i < hi; ++i)
-        if (flag(i)) {
-            mask |= 1u << (i - lo);
-            ++cnt;
-        }
-    uint32_t total;
-    uint32_t r = block_excl_scan<NT>(cnt, s_tmp, total);   // has barriers
-    for (uint32_t i = lo; i < hi; ++i)
-        if (mask & (1u << (i - lo))) emit(i, r++);
-    return total;
+// Bytes a unit counts for against the device's LDS limit: the sizes a call
+// may ask for follow from this (never less than the layout above takes), so
+// that they do not depend on how the kernel arranges its LDS.
+__host__ inline uint32_t dedup_lds_counted(int mode, uint32_t max_idx, uint32_t max_uniq, uint32_t hash_bits,
+                                           uint32_t nt, uint32_t sv_rows) {
+    const uint32_t ids = align16(2 * max_idx), uniq = align16(4 * max_uniq), keys = align16(4 * max_idx);
+    if (mode == kSort) {
+        const uint32_t stab = 2 * keys, end = stab + 3u * 256u * sort_groups(max_idx, nt);
+        return max(max(align16(48 * sv_rows), stab) + ids + uniq, end) + 64;
+    }
+    return max(align16(ids + uniq + 48 * sv_rows), align16(ids + uniq + keys + 2 * align16(4u << hash_bits))) + 64;
 }
 
-// LSD radix sort of a unit's positions by index (Algorithm 2's sort): 8-bit
+// LSD radix sort of a unit's distinct indices (Algorithm 2's sort): 8-bit
 // digits of (index - unit minimum), `passes` of them.  Within a pass, element
 // x of the current order is handled in round x / NT by thread x % NT; its
 // stable destination is the offset of (digit, round, wavefront) plus its
@@ -493,243 +495,443 @@ __device__ __forceinline__ const uint16_t *radix_passes(const uint32_t *s_keys, 
     return src;
 }
 
+// Inserts this thread's corners (row k is pending where bit k is set) into
+// the unit's LDS hash table by linear probing and returns in slot[] where
+// each key sits; fresh gets a bit per row whose key this lane inserted.  The
+// rows advance together, one probe each per round: a round issues every
+// row's compare-and-swap before it looks at the first, so that their LDS
+// round trips overlap.  With MODE kPHash a row still unplaced after A.probes
+// rounds is handed to its whole wavefront, which tests 64 slots at a time.
+template <int MODE>
+__device__ __forceinline__ void insert_rows(const DrawArgs &A, uint32_t *s_table, const uint32_t (&key)[kRows],
+                                            uint32_t (&slot)[kRows], uint32_t pending, uint32_t &fresh) {
+    const uint32_t mask = (1u << A.hash_bits) - 1;
+    fresh = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kRows; ++k) slot[k] = hash_slot(key[k], A.hash_bits);
+    for (uint32_t round = 0; MODE == kPHash ? (pending && round < A.probes) : pending != 0; ++round) {
+        uint32_t prev[kRows];
+#pragma unroll
+        for (uint32_t k = 0; k < kRows; ++k)
+            if (pending & (1u << k)) prev[k] = atomicCAS(&s_table[slot[k]], kEmpty, key[k]);
+#pragma unroll
+        for (uint32_t k = 0; k < kRows; ++k) {
+            if (pending & (1u << k)) {
+                if (prev[k] == kEmpty) fresh |= 1u << k;
+                if (prev[k] == kEmpty || prev[k] == key[k]) pending &= ~(1u << k);
+                else slot[k] = (slot[k] + 1) & mask;
+            }
+        }
+        if (MODE != kPHash && round > mask && pending) {   // table full: only with foreign plans
+            raise_error(A.err, VR_ERR_CAPACITY);
+            break;
+        }
+    }
+    if (MODE != kPHash) return;
+    const uint32_t lane = lane_id();
+#pragma unroll
+    for (uint32_t k = 0; k < kRows; ++k) {
+        uint64_t pend = ballot((pending >> k) & 1u);
+        while (pend) {
+            const uint32_t Lr = (uint32_t)__builtin_ctzll(pend);
+            const uint32_t want = __builtin_amdgcn_readlane(key[k], Lr);
+            uint32_t start = __builtin_amdgcn_readlane(slot[k], Lr);
+            for (uint32_t sweep = 0;; ++sweep) {
+                if (sweep > 2 * (mask + 1)) {     // table full: only with foreign plans
+                    if (lane == 0) raise_error(A.err, VR_ERR_CAPACITY);
+                    break;
+                }
+                const uint32_t s = (start + lane) & mask;
+                const uint32_t val = __hip_atomic_load(&s_table[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                const uint64_t hit = ballot(val == kEmpty || val == want);
+                if (!hit) {
+                    start = (start + kWave) & mask;
+                    continue;
+                }
+                const uint32_t w = (uint32_t)__builtin_ctzll(hit);
+                const uint32_t ws = (start + w) & mask;
+                uint32_t got = 0;
+                if (lane == w) got = atomicCAS(&s_table[ws], kEmpty, want);
+                got = __builtin_amdgcn_readlane(got, w);
+                if (got == kEmpty || got == want) {
+                    if (lane == Lr) {
+                        slot[k] = ws;
+                        if (got == kEmpty) fresh |= 1u << k;
+                    }
+                    break;
+                }
+                start = ws;   // lost the slot to another key: continue past it
+            }
+            pend &= pend - 1;
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Batched deduplication + shading + assembly (Algorithms 2 and 3, and the
 // parallel-hashing variant).  Workgroup u owns unit u (no atomics to pick
 // work); a unit of n corners is deduplicated in LDS into inv unique
 // vertices with canonical local ids:
-//   sort  - ascending rank among distinct indices (Algorithm 2),
+//   sort  - ascending rank among distinct indices (Algorithm 2).  A dynamic
+//           unit's duplicates are dropped by the table first, so that the
+//           radix sort takes its distinct indices only (a quarter of them on
+//           an ordered mesh; on a random one the unit is small either way:
+//           49.4 -> 45.9 us for 398,000 triangles).  A static unit sorts all
+//           of its indices: in random order the table only adds to the sort
+//           (batches of 64: 32.4 us without it, 39.2 us with),
 //   hash  - first-occurrence order (Algorithm 3, ids made independent of
 //           the insertion races by ranking each slot's first position),
 //   phash - as hash, but a lane that fails `probes` linear probes hands its
 //           key to a wavefront-cooperative probe of 64 slots at a time.
+// Corner i of the unit is row i / NT of thread i % NT; a thread's rows stay
+// in registers from the index load to the local ids.  FULL units may have any
+// of the outputs; the others have corners only.  The sort takes at most
+// SORT_ROUNDS indices per thread.
+//
+// A unit is a serial chain (index load, insertion, vertex gather, shading,
+// stores) between barriers, so its phases are kept few and their loads early:
+// the index load covers the clearing of the table, the vertex gather the
+// writing of the local ids.  icosphere of 1.31M triangles, Phong-8, 256 / 341:
+// with the indices staged in LDS, one row at a time and every kernel argument
+// kept in (spilled) scalar registers, hash took 1,245 vector instructions per
+// wavefront and 53.3 us, sort 2,220 and 64.0 us, indexed phash 61.2 us; so
+// hash takes 941 and 51.7 us, sort 1,320 and 57.3 us, indexed phash 50.1 us.
 // ---------------------------------------------------------------------------
-template <int NT, int MODE, int KIND>
-__device__ __forceinline__ void dedup_unit(const DrawArgs &A, const vr_shader_params &sh, uint32_t u, uint32_t nb,
-                                           unsigned char *smem) {
+template <int NT, int MODE, int KIND, bool FULL, uint32_t SORT_ROUNDS>
+__device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint32_t u, uint32_t nb,
+                                           unsigned char *smem, unsigned long long *agg) {
+    constexpr uint32_t NW = NT / kWave, kChunk = kRows * NT;
+    const DrawArgs &A = *(const DrawArgs *)reread(args);
     // without corners, units whose unique vertices would not leave room for
     // several workgroups per CU stream them out through an NT-row stage
-    const bool stream = A.stream_verts != 0;
-    const DedupLds L = dedup_lds_layout(MODE, A.max_idx, A.max_uniq, A.hash_bits, NT, stream ? NT : A.max_uniq);
-    uint32_t *s_keys = (uint32_t *)(smem + L.keys);
+    const bool stream = FULL && A.stream_verts != 0;
+    const bool direct = MODE == kSort && !A.plan;   // the sort takes every corner's index
+    const DedupLds L = dedup_lds_layout(MODE, !direct, A.max_idx, A.max_uniq, A.hash_bits, NT, stream ? NT : A.max_uniq);
     uint16_t *s_local = (uint16_t *)(smem + L.local);
     uint32_t *s_uniq = (uint32_t *)(smem + L.uniq);
     f4 *s_sv = (f4 *)(smem + L.sv);
+    uint32_t *s_table = (uint32_t *)(smem + L.table);
+    uint32_t *s_first = (uint32_t *)(smem + L.first);
     uint32_t *s_tmp = (uint32_t *)(smem + L.tmp);
-    __shared__ uint32_t s_vbase;
+    __shared__ uint32_t s_vbase, s_count, s_min, s_max;
 
-    const uint32_t tid = threadIdx.x, lane = lane_id();
-    {
-        uint32_t t0, t1;
-        batch_range(A, u, t0, t1);
-        uint32_t n = 3 * (t1 - t0);
-        const bool fits = t1 >= t0 && n <= A.max_idx;   // false only for a plan built with other limits
-        if (!fits) {
-            if (tid == 0) raise_error(A.err, VR_ERR_CAPACITY);
-            n = 0;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid / kWave);
+    uint32_t t0, t1;
+    batch_range(A, u, t0, t1);
+    uint32_t n = 3 * (t1 - t0);
+    const bool fits = t1 >= t0 && n <= A.max_idx;   // false only for a plan built with other limits
+    if (!fits) {
+        if (tid == 0) raise_error(A.err, VR_ERR_CAPACITY);
+        n = 0;
+    }
+    // Ids are visible only in the indexed outputs and local ids; then the
+    // hashes make them canonical (first-occurrence order).  Otherwise a key's
+    // id comes from a counter (Algorithm 3), and the corners are the same
+    // either way.  The sort ranks the distinct indices in both cases.
+    const bool canon = FULL && MODE != kSort && (A.need_prefix || A.local_idx);
+    // slots of several chunks wait in LDS; so do the sort's, whose passes need the registers
+    const bool chunked = MODE == kSort || n > kChunk;
+    const uint64_t base = 3ull * t0;
+    uint32_t key[kRows], slot[kRows];
+    auto load_keys = [&](uint32_t c0) {
+#pragma unroll
+        for (uint32_t k = 0; k < kRows; ++k) {
+            const uint32_t i = c0 + k * NT + tid;
+            key[k] = i < n ? A.idx[base + i] : 0u;
         }
-
-        load_indices<NT>(A, 3ull * t0, n, s_keys, tid);
-
-        uint32_t inv;
-        if (MODE == kSort) {
-            // LSD radix sort of the positions by index (radix_passes), only
-            // as many passes as the unit's index range needs
-            uint16_t *s_pos0 = (uint16_t *)(smem + L.pairs);
-            uint16_t *s_pos1 = s_pos0 + A.max_idx;
-            const uint32_t R = (n + NT - 1) / NT;   // <= 8: the launcher sizes NT >= max_idx / 8
-            const uint32_t Gp = sort_groups(A.max_idx, NT);
-            uint32_t *s_c32 = (uint32_t *)(smem + L.stab);                     // [256][Gp] uint8 counts
-            __syncthreads();
-            uint32_t kmin = kEmpty, kmax = 0;
-            for (uint32_t i = tid; i < n; i += NT) {
-                const uint32_t k = s_keys[i];
-                kmin = min(kmin, k);
-                kmax = max(kmax, k);
-                s_pos0[i] = (uint16_t)i;
+    };
+    load_keys(0);   // in flight while the table is cleared
+    if (!direct) {
+        const uint4 e = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
+        const uint32_t q1 = (canon ? 2u : 1u) << A.hash_bits;   // the id words follow the table
+        for (uint32_t q = 4 * tid; q < q1; q += 4 * NT) *(uint4 *)&s_table[q] = e;
+    }
+    // the sort takes a dynamic unit's distinct indices, a static unit's every index
+    const uint32_t sort_cap = direct ? A.max_idx : A.max_uniq, Gp = sort_groups(sort_cap, NT);
+    uint16_t *s_pos0 = (uint16_t *)(smem + L.pairs);
+    uint16_t *s_pos1 = s_pos0 + (align16(4 * sort_cap) / 4);
+    if (MODE == kSort) {
+        uint32_t *s_c32 = (uint32_t *)(smem + L.stab);   // [256][Gp] uint8 counts
+        for (uint32_t i = tid; i < sort_cap; i += NT) s_pos0[i] = (uint16_t)i;
+        for (uint32_t i = tid; i < 64 * Gp; i += NT) s_c32[i] = 0;
+    }
+    if (tid == 0) {
+        s_count = 0;
+        s_min = kEmpty;
+        s_max = 0;
+    }
+    __syncthreads();
+    for (uint32_t c0 = 0; c0 < n; c0 += kChunk) {
+        if (c0) load_keys(c0);
+        uint32_t act = 0, fresh = 0;
+        bool bad = false;
+#pragma unroll
+        for (uint32_t k = 0; k < kRows; ++k) {
+            if (c0 + k * NT + tid < n) act |= 1u << k;
+            if (key[k] >= A.V) {   // replaced by 0, so that no access leaves the buffers
+                bad = true;
+                key[k] = 0;
             }
-            for (uint32_t i = tid; i < 64 * Gp; i += NT) s_c32[i] = 0;
-            block_reduce_minmax<NT>(kmin, kmax, s_tmp);
-            const uint32_t span = n ? kmax - kmin : 0u;
-            const uint32_t passes = span ? (32u - __builtin_clz(span) + 7u) / 8u : 0u;
-            // the round count fixed at compile time where it is small
-            const uint16_t *src;
-            if (R <= 1) src = radix_passes<NT, 1>(s_keys, s_pos0, s_pos1, n, R, kmin, passes, Gp, smem + L.stab, s_tmp);
-            else if (R == 2) src = radix_passes<NT, 2>(s_keys, s_pos0, s_pos1, n, R, kmin, passes, Gp, smem + L.stab, s_tmp);
-            else if (R == 3) src = radix_passes<NT, 3>(s_keys, s_pos0, s_pos1, n, R, kmin, passes, Gp, smem + L.stab, s_tmp);
-            else src = radix_passes<NT, 8>(s_keys, s_pos0, s_pos1, n, R, kmin, passes, Gp, smem + L.stab, s_tmp);
+        }
+        if (bad) raise_error(A.err, VR_ERR_INDEX_RANGE);
+        if (direct) {
+#pragma unroll
+            for (uint32_t k = 0; k < kRows; ++k)
+                if (act & (1u << k)) s_table[c0 + k * NT + tid] = key[k];
+        } else {
+            insert_rows<MODE>(A, s_table, key, slot, act, fresh);
+        }
+        if (canon) {
+#pragma unroll
+            for (uint32_t k = 0; k < kRows; ++k)
+                if (act & (1u << k)) atomicMin(&s_first[slot[k]], c0 + k * NT + tid);
+        } else {
+            // the wavefront's new keys take consecutive ids, one counter update per wavefront
+            uint64_t b[kRows];
+            uint32_t total = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < kRows; ++k) {
+                b[k] = ballot((fresh >> k) & 1u);
+                total += (uint32_t)__popcll(b[k]);
+            }
+            if (total) {
+                uint32_t id0 = 0;
+                if (lane == 0) id0 = atomicAdd(&s_count, total);
+                id0 = __builtin_amdgcn_readfirstlane(id0);
+#pragma unroll
+                for (uint32_t k = 0; k < kRows; ++k) {
+                    if (fresh & (1u << k)) {
+                        const uint32_t id = id0 + __builtin_amdgcn_mbcnt_hi(
+                                                      (uint32_t)(b[k] >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)b[k], 0u));
+                        s_first[slot[k]] = id;
+                        if (id < A.max_uniq) s_uniq[id] = key[k];
+                    }
+                    id0 += (uint32_t)__popcll(b[k]);
+                }
+            }
+            if (MODE == kSort) {   // the range of the unit's indices
+                uint32_t mn = kEmpty, mx = 0;
+#pragma unroll
+                for (uint32_t k = 0; k < kRows; ++k) {
+                    if (act & (1u << k)) {
+                        mn = min(mn, key[k]);
+                        mx = max(mx, key[k]);
+                    }
+                }
+                mn = wave_min(mn);
+                mx = wave_max(mx);
+                if (lane == 0) {
+                    atomicMin(&s_min, mn);
+                    atomicMax(&s_max, mx);
+                }
+            }
+        }
+        if (chunked && !direct) {
+#pragma unroll
+            for (uint32_t k = 0; k < kRows; ++k)
+                if (act & (1u << k)) s_local[c0 + k * NT + tid] = (uint16_t)slot[k];
+        }
+    }
+    __syncthreads();
+    // the rows of chunk c0: their slots, from LDS when there are several chunks
+    auto row_slots = [&](uint32_t c0) {
+        if (!chunked) return;
+#pragma unroll
+        for (uint32_t k = 0; k < kRows; ++k) {
+            const uint32_t i = c0 + k * NT + tid;
+            slot[k] = i < n ? (uint32_t)s_local[i] : 0u;
+        }
+    };
+    uint32_t inv = 0;
+    if (canon) {
+        // a slot's id is the rank of its first position: positions are in
+        // (row, wavefront, lane) order, so a ballot per row and the counts of
+        // the rows and wavefronts before give it.  The first position then
+        // overwrites its slot's word with the rank r <= position, which no
+        // later position can mistake for itself.
+        uint8_t *s_cnt = (uint8_t *)s_tmp;   // [kRows][NW], at most 64 each
+        for (uint32_t c0 = 0; c0 < n; c0 += kChunk) {
+            row_slots(c0);
+            uint64_t b[kRows];
+#pragma unroll
+            for (uint32_t k = 0; k < kRows; ++k) {
+                const uint32_t i = c0 + k * NT + tid;
+                b[k] = ballot(i < n && s_first[slot[k]] == i);
+                if (lane == 0) s_cnt[k * NW + w] = (uint8_t)__popcll(b[k]);
+            }
+            __syncthreads();
+#pragma unroll
+            for (uint32_t k = 0; k < kRows; ++k) {
+                uint32_t before = inv, all = 0;
+                if (NW < 4) {
+#pragma unroll
+                    for (uint32_t j = 0; j < NW; ++j) {
+                        const uint32_t c = s_cnt[k * NW + j];
+                        before += j < w ? c : 0u;
+                        all += c;
+                    }
+                } else {
+#pragma unroll
+                    for (uint32_t j = 0; j < NW; j += 4) {   // four wavefronts' counts per word
+                        const uint32_t c = ((const uint32_t *)s_cnt)[(k * NW + j) / 4];
+                        const uint32_t low = w <= j ? 0u : w - j >= 4 ? ~0u : (1u << (8 * (w - j))) - 1u;
+                        before = __builtin_amdgcn_sad_u8(c & low, 0u, before);
+                        all = __builtin_amdgcn_sad_u8(c, 0u, all);
+                    }
+                }
+                if ((b[k] >> lane) & 1ull) {
+                    const uint32_t r = before + __builtin_amdgcn_mbcnt_hi(
+                                                    (uint32_t)(b[k] >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)b[k], 0u));
+                    s_first[slot[k]] = r;
+                    if (r < A.max_uniq) s_uniq[r] = chunked ? s_table[slot[k]] : key[k];
+                }
+                inv += all;
+            }
+            if (chunked) __syncthreads();   // the counts are read before the next chunk's
+        }
+        __syncthreads();
+    } else {
+        inv = s_count;
+    }
+    if (inv > A.max_uniq) {   // only with a plan built for a larger N_u
+        if (tid == 0) raise_error(A.err, VR_ERR_CAPACITY);
+        inv = 0;
+        n = 0;
+    }
+    // this unit's invocation count is published as soon as it is known, since
+    // the units after it wait for it (random order, phash 128 / 128, every
+    // output: 80.9 us when published after the local ids, 72.2 us here), and
+    // its prefix is resolved after shading (before it when the shaded vertices
+    // stream out)
+    auto publish = [&]() {
+        if (FULL && A.need_prefix && tid == 0) lookback_publish(A.status, u, (1ull << 32) | inv);
+    };
+    if (!direct) publish();
+    const uint16_t *s_rank = nullptr;
+    if (MODE == kSort) {
+        // LSD radix sort (radix_passes) of the distinct indices, or of a static
+        // unit's every index, only as many passes as the unit's index range needs
+        const uint32_t m = direct ? n : inv;
+        const uint32_t *s_keys = direct ? s_table : s_uniq;
+        const uint32_t R = (m + NT - 1) / NT;   // the launcher sizes NT for at most 8
+        const uint32_t kmin = s_min, span = m ? s_max - kmin : 0u;
+        const uint32_t passes = span ? (32u - __builtin_clz(span) + 7u) / 8u : 0u;
+        // the round count fixed at compile time where it is small
+        auto sorted_by = [&](auto rr) {
+            return radix_passes<NT, decltype(rr)::value>(s_keys, s_pos0, s_pos1, m, R, kmin, passes, Gp,
+                                                         smem + L.stab, s_tmp);
+        };
+        const uint16_t *src;
+        if (R <= 1) src = sorted_by(std::integral_constant<uint32_t, 1>{});
+        else if (R == 2) src = sorted_by(std::integral_constant<uint32_t, 2>{});
+        else if (SORT_ROUNDS == 3 || R == 3) src = sorted_by(std::integral_constant<uint32_t, 3>{});
+        else src = sorted_by(std::integral_constant<uint32_t, 8>{});
+        if (direct) {
             // run ends of the sorted indices; the exclusive prefix over run
             // ends is the rank of every entry's run (Algorithm 2's marks and
             // prefix sum)
-            __syncthreads();
             const uint32_t E = (n + NT - 1) / NT;
             const uint32_t lo = min(n, tid * E), hi = min(n, lo + E);
             uint32_t cnt = 0;
             for (uint32_t i = lo; i < hi; ++i) cnt += (i + 1 == n || s_keys[src[i]] != s_keys[src[i + 1]]);
             uint32_t r = block_excl_scan<NT>(cnt, s_tmp, inv);
+            publish();
             for (uint32_t i = lo; i < hi; ++i) {
                 const uint32_t p = src[i], k = s_keys[p];
                 s_local[p] = (uint16_t)r;
                 if (i + 1 == n || k != s_keys[src[i + 1]]) s_uniq[r++] = k;
             }
         } else {
-            uint32_t *s_table = (uint32_t *)(smem + L.table);
-            uint32_t *s_first = (uint32_t *)(smem + L.first);
-            const uint32_t S = 1u << A.hash_bits, mask = S - 1;
-            // Ids are visible only in the indexed outputs and local ids; then
-            // they are made canonical (first-occurrence order).  Otherwise a
-            // key's id comes from a counter taken by the lane that inserted
-            // it (Algorithm 3), and the corners are the same either way.
-            const bool canon = A.need_prefix || A.local_idx;
-            __shared__ uint32_t s_count;
-            for (uint32_t s = tid; s < S; s += NT) {
-                s_table[s] = kEmpty;
-                s_first[s] = kEmpty;
+            // an id's place in the sorted order is its rank
+            uint16_t *s_out = src == s_pos0 ? s_pos1 : s_pos0;   // free after the last pass
+            for (uint32_t i = tid; i < inv; i += NT) {
+                const uint32_t id = src[i];
+                s_table[i] = s_uniq[id];   // the keys' table is dead, the id words are not
+                s_out[id] = (uint16_t)i;
             }
-            if (tid == 0) s_count = 0;
-            __syncthreads();
-            // the inserting lane of a new key takes the next id
-            auto take_id = [&](uint32_t slot, uint32_t key) {
-                const uint32_t id = atomicAdd(&s_count, 1u);
-                s_first[slot] = id;
-                if (id < A.max_uniq) s_uniq[id] = key;
-            };
-            if (MODE == kHash) {
-                for (uint32_t i = tid; i < n; i += NT) {
-                    const uint32_t k = s_keys[i];
-                    uint32_t p = hash_slot(k, A.hash_bits);
-                    for (uint32_t probe = 0;; ++probe) {   // linear probing; S >= distinct keys
-                        const uint32_t prev = atomicCAS(&s_table[p], kEmpty, k);
-                        if (prev == kEmpty && !canon) take_id(p, k);
-                        if (prev == kEmpty || prev == k) break;
-                        if (probe >= mask) {              // table full: only with foreign plans
-                            raise_error(A.err, VR_ERR_CAPACITY);
-                            break;
-                        }
-                        p = (p + 1) & mask;
-                    }
-                    s_local[i] = (uint16_t)p;
-                    if (canon) atomicMin(&s_first[p], i);
-                }
-            } else {
-                // wave-uniform sweep so the cooperative path sees every lane
-                for (uint32_t base = (tid / kWave) * kWave; base < n; base += NT) {
-                    const uint32_t i = base + lane;
-                    const bool act = i < n;
-                    const uint32_t k = act ? s_keys[i] : 0u;
-                    uint32_t p = hash_slot(k, A.hash_bits);
-                    uint32_t slot = 0;
-                    bool placed = !act;
-                    for (uint32_t r = 0; r < A.probes && !placed; ++r) {
-                        const uint32_t prev = atomicCAS(&s_table[p], kEmpty, k);
-                        if (prev == kEmpty && !canon) take_id(p, k);
-                        if (prev == kEmpty || prev == k) {
-                            slot = p;
-                            placed = true;
-                        } else {
-                            p = (p + 1) & mask;
-                        }
-                    }
-                    uint64_t pend = ballot(!placed);
-                    while (pend) {
-                        const uint32_t Lr = (uint32_t)__ffsll((long long)pend) - 1;
-                        const uint32_t key = __builtin_amdgcn_readlane(k, Lr);
-                        uint32_t start = __builtin_amdgcn_readlane(p, Lr);
-                        for (uint32_t sweep = 0;; ++sweep) {
-                            if (sweep > 2 * (mask + 1)) {     // table full: only with foreign plans
-                                if (lane == 0) raise_error(A.err, VR_ERR_CAPACITY);
-                                break;
-                            }
-                            const uint32_t s = (start + lane) & mask;
-                            const uint32_t val = __hip_atomic_load(&s_table[s], __ATOMIC_RELAXED,
-                                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-                            const uint64_t hit = ballot(val == kEmpty || val == key);
-                            if (!hit) {
-                                start = (start + kWave) & mask;
-                                continue;
-                            }
-                            const uint32_t w = (uint32_t)__ffsll((long long)hit) - 1;
-                            const uint32_t ws = (start + w) & mask;
-                            uint32_t got = 0;
-                            if (lane == w) {
-                                got = atomicCAS(&s_table[ws], kEmpty, key);
-                                if (got == kEmpty && !canon) take_id(ws, key);
-                            }
-                            got = __builtin_amdgcn_readlane(got, w);
-                            if (got == kEmpty || got == key) {
-                                if (lane == Lr) {
-                                    slot = ws;
-                                    placed = true;
-                                }
-                                break;
-                            }
-                            start = ws;   // lost the slot to another key: continue past it
-                        }
-                        pend &= pend - 1;
-                    }
-                    if (act) {
-                        s_local[i] = (uint16_t)slot;
-                        if (canon) atomicMin(&s_first[slot], i);
-                    }
-                }
-            }
-            __syncthreads();
-            if (canon) {
-                // canonical ids: a slot's id is the rank of its first position;
-                // every flag is read before the scan's barriers, so the first
-                // position can overwrite its slot's word with the rank
-                inv = rank_flagged<NT>(
-                    n, s_tmp, [&](uint32_t i) { return s_first[s_local[i]] == i; },
-                    [&](uint32_t i, uint32_t r) {
-                        s_uniq[r] = s_keys[i];
-                        s_first[s_local[i]] = r;
-                    });
-                __syncthreads();
-            } else {
-                inv = s_count;
-            }
-            for (uint32_t i = tid; i < n; i += NT) s_local[i] = (uint16_t)s_first[s_local[i]];
+            __syncthreads();   // every index is read before the list is rewritten in order
+            for (uint32_t i = tid; i < inv; i += NT) s_uniq[i] = s_table[i];
+            s_rank = s_out;
         }
-
-        if (inv > A.max_uniq) {   // only with a plan built for a larger N_u
-            if (tid == 0) raise_error(A.err, VR_ERR_CAPACITY);
-            inv = 0;
-        }
-        // publish this unit's invocation count early; resolve after shading
-        // (before it when the shaded vertices stream out)
-        if (A.need_prefix && tid == 0) lookback_publish(A.status, u, (1ull << 32) | inv);
-        __syncthreads();
-        if (!stream)
-            for (uint32_t j = tid; j < inv; j += NT) shade_to_lds<KIND>(A, sh, s_uniq[j], s_sv + 3 * j);
-        if (tid < kWave) {   // the first wavefront, whole (NT >= 64)
-            uint32_t vb = 0;
-            if (A.need_prefix) vb = (uint32_t)lookback_resolve(A.status, u, (1ull << 32) | inv, A.err);
-            if (tid == 0) {
-                s_vbase = vb;
-                if (A.unit_offsets && u + 1 == nb) A.unit_offsets[nb] = A.T;
-            }
-        }
-        __syncthreads();
-        if (stream) {
-            // NT unique vertices at a time: shaded into the stage, then stored
-            // as one contiguous span of rows
-            f4 *dst = A.verts ? A.verts + 3ull * s_vbase : nullptr;
-            for (uint32_t j0 = 0; j0 < inv; j0 += NT) {
-                const uint32_t rows = min((uint32_t)NT, inv - j0);
-                if (tid < rows) shade_to_lds<KIND>(A, sh, s_uniq[j0 + tid], s_sv + 3 * tid);
-                __syncthreads();
-                if (dst)
-                    for (uint32_t q = tid; q < 3 * rows; q += NT)
-                        __builtin_nontemporal_store(s_sv[q], dst + 3ull * j0 + q);
-                __syncthreads();
-            }
-        }
-        if (fits && (inv > 0 || n == 0))
-            write_unit<NT>(A, t0, t1 - t0, s_local, s_sv, inv, s_vbase, u, tid, stream);
-        if (tid == 0 && A.agg) A.agg[u] = (1ull << 32) | inv;
-        __syncthreads();   // the caller may reuse the LDS for the next unit
+        __syncthreads();   // the list is complete
     }
+    // the first NT unique vertices: their input is loaded while the corners'
+    // local ids are written
+    f4 va = {}, vb = {};
+    if (!stream && tid < inv) {
+        const uint32_t v = s_uniq[tid];
+        va = A.vtx[2ull * v];
+        vb = A.vtx[2ull * v + 1];
+    }
+    for (uint32_t c0 = 0; c0 < n && !direct; c0 += kChunk) {
+        row_slots(c0);
+#pragma unroll
+        for (uint32_t k = 0; k < kRows; ++k) {
+            const uint32_t i = c0 + k * NT + tid;
+            if (i < n) {
+                uint32_t id = s_first[slot[k]];
+                if (MODE == kSort) id = s_rank[id];
+                s_local[i] = (uint16_t)id;
+            }
+        }
+    }
+    if (!direct) __syncthreads();   // the table is dead: shaded vertices take its space
+    const DrawArgs &B = *(const DrawArgs *)reread(args);
+    const vr_shader_params &sh = *(const vr_shader_params *)reread(shader);
+    if (!stream) {
+        if (tid < inv) shade_raw_to_lds<KIND>(sh, va, vb, s_sv + 3 * tid);
+        for (uint32_t j = tid + NT; j < inv; j += NT) shade_to_lds<KIND>(B, sh, s_uniq[j], s_sv + 3 * j);
+    }
+    if (FULL && tid < kWave) {   // the first wavefront, whole (NT >= 64)
+        uint32_t vb0 = 0;
+        if (B.need_prefix) vb0 = (uint32_t)lookback_resolve(B.status, u, (1ull << 32) | inv, B.err);
+        if (tid == 0) {
+            s_vbase = vb0;
+            if (B.unit_offsets && u + 1 == nb) B.unit_offsets[nb] = B.T;
+        }
+    }
+    __syncthreads();
+    if (stream) {
+        // NT unique vertices at a time: shaded into the stage, then stored as
+        // one contiguous span of rows while the next ones' input is loaded
+        f4 *dst = B.verts ? B.verts + 3ull * s_vbase : nullptr;
+        f4 ra = {}, rb = {};
+        auto load_next = [&](uint32_t j) {
+            if (j >= inv) return;
+            const uint32_t v = s_uniq[j];
+            ra = B.vtx[2ull * v];
+            rb = B.vtx[2ull * v + 1];
+        };
+        load_next(tid);
+        for (uint32_t j0 = 0; j0 < inv; j0 += NT) {
+            const uint32_t rows = min((uint32_t)NT, inv - j0);
+            if (tid < rows) shade_raw_to_lds<KIND>(sh, ra, rb, s_sv + 3 * tid);
+            __syncthreads();
+            load_next(j0 + NT + tid);
+            if (dst)
+                for (uint32_t q = tid; q < 3 * rows; q += NT)
+                    __builtin_nontemporal_store(s_sv[q], dst + 3ull * j0 + q);
+            __syncthreads();
+        }
+    }
+    if (fits && (inv > 0 || t1 == t0))
+        write_unit<NT, FULL>(B, t0, t1 - t0, s_local, s_sv, inv, FULL ? s_vbase : 0u, u, tid, stream);
+    if (tid == 0) agg[u] = (1ull << 32) | inv;
+    __syncthreads();   // the caller may reuse the LDS for the next unit
 }
+
+// Wavefronts per SIMD the occupancy-bound kernels are held to: as many as
+// their registers allow without spilling to scratch (FULL at 8 spilled 40 B a
+// lane: indexed phash 128 / 128 36.7 us at 8, 35.0 us at 7).
+__host__ __device__ constexpr int dedup_waves(int mode, bool full) { return mode == kSort || full ? 7 : 8; }
+
+struct DedupLaunch {
+    DrawArgs A;
+    vr_shader_params sh;
+    uint32_t base, stride;
+};
 
 // Units from base on: unit base + workgroup index (stride 0), or
 // grid-stride over every unit from base on (stride = the grid).  Grid-stride
@@ -741,13 +943,16 @@ __device__ __forceinline__ void dedup_unit(const DrawArgs &A, const vr_shader_pa
 // LDS lets that many workgroups reside, and then the extra wavefronts hide
 // more of a unit's serial latency; otherwise the bound would only add
 // spills.
-template <int NT, int MODE, int KIND, bool OCC>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC ? (MODE == kSort ? 7 : 8) : 1))) void k_dedup(DrawArgs A, vr_shader_params sh, uint32_t base, uint32_t stride) {
+template <int NT, int MODE, int KIND, bool OCC, bool FULL>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC ? dedup_waves(MODE, FULL) : MODE == kSort ? 5 : 6))) void k_dedup(DedupLaunch) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (base == 0) clear_counters(A);
+    // the launch's only argument, at the start of the kernel-argument segment
+    const VR_CONSTANT DedupLaunch *P = (const VR_CONSTANT DedupLaunch *)__builtin_amdgcn_kernarg_segment_ptr();
+    const DrawArgs &A = *(const DrawArgs *)&P->A;
+    if (P->base == 0) clear_counters(A);
     const uint32_t nb = launch_units(A, batch_count(A));
-    for (uint64_t u = (uint64_t)base + blockIdx.x; u < nb; u += stride ? stride : nb)
-        dedup_unit<NT, MODE, KIND>(A, sh, (uint32_t)u, nb, smem);
+    for (uint64_t u = (uint64_t)P->base + blockIdx.x; u < nb; u += P->stride ? P->stride : nb)
+        dedup_unit<NT, MODE, KIND, FULL, OCC ? 3 : 8>(&P->A, &P->sh, (uint32_t)u, nb, smem, A.agg);
 }
 
 // ---------------------------------------------------------------------------
@@ -876,7 +1081,7 @@ __device__ __forceinline__ uint32_t ballot_round(const DrawArgs &A, uint32_t t0,
 // wavefronts of a workgroup can work on different batches.
 template <int KIND>
 __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_params &sh, uint32_t b, uint32_t nb,
-                                             unsigned char *lds) {
+                                             unsigned char *lds, unsigned long long *agg_out) {
     const uint32_t lane = lane_id();
     uint32_t t0, t1;
     batch_range(A, b, t0, t1);
@@ -913,14 +1118,14 @@ __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_
         const uint32_t end = ballot_round(A, t0, cur, t1, s_keys, pre, s_new, s_map, st);
         if (lane < st.fill) shade_raw_to_lds<KIND>(sh, st.va, st.vb, s_sv + 3 * lane);
         wave_sync_lds();
-        write_unit<64>(A, cur, end - cur, s_map, s_sv, st.fill, vbase, ubase + r, lane);
+        write_unit<64, true>(A, cur, end - cur, s_map, s_sv, st.fill, vbase, ubase + r, lane);
         wave_sync_lds();
         vbase += st.fill;
         inv += st.fill;
         cur = end;
     }
     if (A.unit_offsets && b + 1 == nb && lane == 0) A.unit_offsets[ubase + r] = A.T;
-    if (lane == 0 && A.agg) A.agg[b] = ((unsigned long long)r << 32) | inv;
+    if (lane == 0) agg_out[b] = ((unsigned long long)r << 32) | inv;
 }
 
 // Two wavefronts per workgroup, one batch each (batch 2 * workgroup +
@@ -936,7 +1141,7 @@ __global__ __launch_bounds__(kBallotWaves * 64) void k_ballot(DrawArgs A, vr_sha
     const uint32_t w = threadIdx.x / kWave;
     const uint32_t b = blockIdx.x * kBallotWaves + w;
     if (b >= nb) return;   // only wavefront-level synchronisation follows
-    ballot_batch<KIND>(A, sh, b, nb, smem + w * stride);
+    ballot_batch<KIND>(A, sh, b, nb, smem + w * stride, A.agg);
 }
 
 }  // namespace vr

@@ -178,6 +178,7 @@ uint32_t log2u(uint32_t x) {
 
 struct Resolved {
     uint32_t nu = 0, nt = 0, max_idx = 0, max_uniq = 0, hash_bits = 0, probes = 4;
+    uint32_t size_nt = 0, size_bits = 0;   // threads and table size the LDS limit is counted with
 };
 
 vr_status check_args(vr_ctx *c, uint64_t num_indices, uint32_t num_vertices, const vr_shader_params *sh,
@@ -229,18 +230,36 @@ vr_status check_args(vr_ctx *c, uint64_t num_indices, uint32_t num_vertices, con
                     (unsigned long long)units_bound(strategy, T, batch_tris));
     // launch shape (never changes results)
     if (strategy != VR_NAIVE && strategy != VR_MULTI && !is_ballot(strategy)) {
-        uint32_t want = o.wg_size ? o.wg_size : std::max<uint32_t>(64, std::min<uint32_t>(256, r.max_uniq));
-        uint32_t nt = 64;
-        while (nt * 2 <= want && nt < 1024) nt *= 2;
-        // the sort keeps at most 8 rounds of elements per thread in registers;
-        // the canonical ranking keeps at most 32 flags per thread in a mask
+        auto threads = [](uint32_t want) {
+            uint32_t nt = 64;
+            while (nt * 2 <= want && nt < 1024) nt *= 2;
+            return nt;
+        };
+        // the sizes a unit may have: at most 8 indices per thread for the sort,
+        // 32 for the hashes, and the LDS counted with that many threads
+        uint32_t nt = threads(o.wg_size ? o.wg_size : std::max<uint32_t>(64, std::min<uint32_t>(256, r.max_uniq)));
         const uint32_t per = (strategy == VR_STATIC_SORT || strategy == VR_DYN_SORT) ? 8u : 32u;
         while (nt * per < r.max_idx && nt < 1024) nt *= 2;
         if (nt * per < r.max_idx)
             return fail(c, VR_ERR_ARG, "batch_tris %u: a unit of %u indices needs more than 1024 threads", batch_tris,
                         r.max_idx);
-        r.nt = nt;
-        const uint32_t slots = o.hash_slots ? o.hash_slots : std::max<uint32_t>(8, 1u << log2u(2 * r.max_uniq));
+        r.size_nt = r.nt = nt;
+        // a unit is deduplicated from registers, kRows corners per thread: by
+        // default at least as many threads as hold a whole unit (hash 1024 /
+        // 1365, Hilbert order: 30.3 us with 256 threads, 23.6 us with 1024);
+        // not fewer than before where the LDS of the worst case limits the
+        // workgroups (static 85: 13.4 us with 64 threads, 11.2 us with 128)
+        if (!o.wg_size) r.nt = std::max(nt, threads(1u << log2u((r.max_idx + kRows - 1) / kRows)));
+        uint32_t slots = o.hash_slots ? o.hash_slots : std::max<uint32_t>(8, 1u << log2u(2 * r.max_uniq));
+        r.size_bits = log2u(slots);
+        // twice the slots (at most a third full instead of a half) shorten the
+        // probes and cost no LDS where the table shares the space of the shaded
+        // vertices (8 B per slot, 48 B per vertex; all are kept for corners, at
+        // least a workgroup's worth otherwise): static 85 in random order
+        // 42.8 us half full, 27.0 us so, in Hilbert order the same
+        const uint32_t more = 1u << log2u(3 * r.max_uniq);
+        if (!o.hash_slots && more <= VR_MAX_HASH_SLOTS && (out->corners || r.max_uniq <= 768 || 8 * more <= 48 * r.nt))
+            slots = std::max<uint32_t>(slots, more);
         r.hash_bits = log2u(slots);
         r.probes = o.hash_probes ? o.hash_probes : 4;
     } else {
@@ -256,32 +275,43 @@ vr_status check_args(vr_ctx *c, uint64_t num_indices, uint32_t num_vertices, con
 // fewest; without prefix outputs (units in any order) the same workgroups
 // take the rest grid-stride, else a second launch has one workgroup per
 // possible further unit.
-template <int NT, int MODE, int KIND, bool OCC>
-void launch_dedup(vr_ctx *c, const DrawArgs &A, const vr_shader_params &sh, uint32_t lds, uint64_t units) {
+template <int NT, int MODE, int KIND, bool OCC, bool FULL>
+void launch_dedup_as(vr_ctx *c, const DrawArgs &A, const vr_shader_params &sh, uint32_t lds, uint64_t units) {
     uint64_t first = units;
     if (A.plan) first = std::min<uint64_t>(units, (A.T + A.batch_tris - 1) / A.batch_tris);
     const bool stride = A.plan && !A.need_prefix && first > 0 && units > first;
     if (first)
-        hipLaunchKernelGGL((k_dedup<NT, MODE, KIND, OCC>), dim3((uint32_t)first), dim3(NT), lds, c->stream, A, sh,
-                           0u, stride ? (uint32_t)first : 0u);
+        hipLaunchKernelGGL((k_dedup<NT, MODE, KIND, OCC, FULL>), dim3((uint32_t)first), dim3(NT), lds, c->stream,
+                           (DedupLaunch{A, sh, 0u, stride ? (uint32_t)first : 0u}));
     if (units > first && !stride)
-        hipLaunchKernelGGL((k_dedup<NT, MODE, KIND, OCC>), dim3((uint32_t)(units - first)), dim3(NT), lds,
-                           c->stream, A, sh, (uint32_t)first, 0u);
+        hipLaunchKernelGGL((k_dedup<NT, MODE, KIND, OCC, FULL>), dim3((uint32_t)(units - first)), dim3(NT), lds,
+                           c->stream, (DedupLaunch{A, sh, (uint32_t)first, 0u}));
+}
+
+// Draws with corners and counters only take kernels compiled without the
+// other outputs.
+bool corners_only(const DrawArgs &A) { return A.corners && !A.need_prefix && !A.local_idx; }
+
+template <int NT, int MODE, int KIND, bool OCC>
+void launch_dedup(vr_ctx *c, const DrawArgs &A, const vr_shader_params &sh, uint32_t lds, uint64_t units) {
+    if (corners_only(A)) launch_dedup_as<NT, MODE, KIND, OCC, false>(c, A, sh, lds, units);
+    else launch_dedup_as<NT, MODE, KIND, OCC, true>(c, A, sh, lds, units);
 }
 
 // Whether a dedup launch of nt threads and lds bytes per workgroup takes the
 // occupancy-bound kernel: only for 128 and 256 threads, and only when the
 // LDS lets eight wavefronts per SIMD reside (seven for the sort).
-bool dedup_occupancy_bound(const vr_ctx *c, int mode, uint32_t nt, uint32_t lds) {
+bool dedup_occupancy_bound(const vr_ctx *c, int mode, uint32_t nt, uint32_t lds, uint32_t sort_max, bool full) {
     if (nt != 128 && nt != 256) return false;
-    const uint32_t target = mode == kSort ? 7u : 8u;          // wavefronts per SIMD
+    if (mode == kSort && sort_max > 3 * nt) return false;     // its sort takes three rounds
+    const uint32_t target = (uint32_t)dedup_waves(mode, full);   // wavefronts per SIMD
     const uint32_t groups = target * 4u / (nt / kWave);        // workgroups per CU for them
     return (uint64_t)groups * (lds + 64u) <= c->lds_limit;     // + the kernel's static LDS
 }
 
 template <int MODE, int KIND>
 void dispatch_nt(vr_ctx *c, uint32_t nt, const DrawArgs &A, const vr_shader_params &sh, uint32_t lds, uint64_t units) {
-    const bool occ = dedup_occupancy_bound(c, MODE, nt, lds);
+    const bool occ = dedup_occupancy_bound(c, MODE, nt, lds, A.plan ? A.max_uniq : A.max_idx, !corners_only(A));
     switch (nt) {
     case 64: launch_dedup<64, MODE, KIND, false>(c, A, sh, lds, units); break;
     case 128:
@@ -523,7 +553,7 @@ template <int MODE, int KIND, bool OCC>
 void launch_frame_variant(const FrameLaunch &L, const FrameVariant &v, hipStream_t s) {
     hipLaunchKernelGGL((k_frame<MODE, KIND, OCC>), dim3(v.grid), dim3(kFrameNT), v.lds_total, s, L.draws, L.order,
                        v.lo, v.hi, L.shaders, (const uint32_t *)L.unit_base, (const uint32_t *)L.slot_base, L.agg,
-                       v.unit_lds, v.ballot_stride, L.err, L.total_inv);
+                       v.unit_lds, v.ballot_stride);
 }
 
 template <int MODE, int KIND, bool OCC>
@@ -608,14 +638,19 @@ uint32_t frame_mode(vr_strategy s) {
 struct FrameNeeds {
     uint64_t slots = 0, units = 0;
     uint32_t unit_lds = 256 * 48, ballot_stride = 0;
+    uint32_t counted_lds = 0;   // what the units count for against the LDS limit
     bool index_error = false;
     uint32_t lds_total(uint32_t n) const {
         return align16(std::max(unit_lds, 4 * ballot_stride)) + 4 * (n + 1);
+    }
+    uint32_t lds_counted(uint32_t n) const {
+        return align16(std::max(std::max(unit_lds, counted_lds), 4 * ballot_stride)) + 4 * (n + 1);
     }
     void merge(const FrameNeeds &o) {
         slots += o.slots;
         units += o.units;
         unit_lds = std::max(unit_lds, o.unit_lds);
+        counted_lds = std::max(counted_lds, o.counted_lds);
         ballot_stride = std::max(ballot_stride, o.ballot_stride);
         index_error = index_error || o.index_error;
     }
@@ -623,7 +658,7 @@ struct FrameNeeds {
 
 // Validates one frame entry and fills its device descriptor.
 vr_status describe_draw(vr_ctx *c, const vr_draw &D, const vr_shader_params &sh, uint32_t d, DrawDesc &X,
-                        FrameNeeds &need) {
+                        FrameNeeds &need, uint32_t *err) {
     vr_opts o{};
     o.max_unique = D.max_unique;
     o.d_plan = D.d_plan;
@@ -644,27 +679,29 @@ vr_status describe_draw(vr_ctx *c, const vr_draw &D, const vr_shader_params &sh,
         return fail(c, VR_ERR_ARG, "draw %u: a dynamic draw in a frame needs its plan", d);
     if (T && D.num_vertices == 0) need.index_error = true;
     X = DrawDesc{};
-    X.idx = D.d_indices;
-    X.vtx = (const f4 *)D.d_vertices;
-    X.corners = (f4 *)D.d_corners;
-    X.counters = (unsigned long long *)D.d_counters;
-    X.plan = is_dynamic(D.strategy) ? D.d_plan : nullptr;
-    X.V = D.num_vertices;
-    X.T = (T && D.num_vertices == 0) ? 0u : (uint32_t)T;
-    X.batch_tris = D.batch_tris;
-    X.num_batches = is_dynamic(D.strategy) ? 0u : (uint32_t)((T + D.batch_tris - 1) / D.batch_tris);
+    X.A.idx = D.d_indices;
+    X.A.vtx = (const f4 *)D.d_vertices;
+    X.A.corners = (f4 *)D.d_corners;
+    X.A.counters = (unsigned long long *)D.d_counters;
+    X.A.plan = is_dynamic(D.strategy) ? D.d_plan : nullptr;
+    X.A.V = D.num_vertices;
+    X.A.T = (T && D.num_vertices == 0) ? 0u : (uint32_t)T;
+    X.A.batch_tris = D.batch_tris;
+    X.A.num_batches = is_dynamic(D.strategy) ? 0u : (uint32_t)((T + D.batch_tris - 1) / D.batch_tris);
     X.shader = D.shader;
     X.mode = frame_mode(D.strategy);
     X.kind = sh.kind;
-    X.max_idx = r.max_idx;
-    X.max_uniq = r.max_uniq;
-    X.hash_bits = r.hash_bits;
-    X.probes = r.probes;
+    X.A.max_idx = r.max_idx;
+    X.A.max_uniq = r.max_uniq;
+    X.A.hash_bits = r.hash_bits;
+    X.A.probes = r.probes;
+    X.A.err = err;
+    X.A.status_cap = 0xFFFFFFFFu;
     if (X.mode == kFrameNaive) {
         need.slots += (3 * T + 255) / 256;
         need.units += (3 * T + 255) / 256;
     } else {
-        const uint64_t nb = is_dynamic(D.strategy) ? dyn_batch_bound(T, r.nu, D.batch_tris) : X.num_batches;
+        const uint64_t nb = is_dynamic(D.strategy) ? dyn_batch_bound(T, r.nu, D.batch_tris) : X.A.num_batches;
         X.slot_cap = (uint32_t)std::min<uint64_t>(nb, 0xFFFFFFFFull);
         need.slots += nb;
         if (X.mode == kFrameBallot) {
@@ -677,8 +714,10 @@ vr_status describe_draw(vr_ctx *c, const vr_draw &D, const vr_shader_params &sh,
             if (r.max_idx > per * kFrameNT)
                 return fail(c, VR_ERR_ARG, "draw %u: batches of %u triangles are too large for a frame", d,
                             D.batch_tris);
-            need.unit_lds = std::max(need.unit_lds, dedup_lds_layout((int)X.mode, r.max_idx, r.max_uniq, r.hash_bits,
+            need.unit_lds = std::max(need.unit_lds, dedup_lds_layout((int)X.mode, is_dynamic(D.strategy), r.max_idx, r.max_uniq, r.hash_bits,
                                                                      kFrameNT, r.max_uniq).total);
+            need.counted_lds = std::max(need.counted_lds, dedup_lds_counted((int)X.mode, r.max_idx, r.max_uniq,
+                                                                            r.size_bits, kFrameNT, r.max_uniq));
         }
     }
     return VR_OK;
@@ -710,9 +749,9 @@ vr_status frame_variants(vr_ctx *c, const DrawDesc *desc, const FrameNeeds *need
         v.ballot_stride = need.ballot_stride;
         v.unit_lds = align16(std::max(need.unit_lds, 4 * need.ballot_stride));
         v.lds_total = need.lds_total(hi - lo);
-        if (v.lds_total > c->lds_limit)
-            return fail(c, VR_ERR_ARG, "frame variant needs %u B of LDS per workgroup (limit %zu)", v.lds_total,
-                        c->lds_limit);
+        if (need.lds_counted(hi - lo) > c->lds_limit)
+            return fail(c, VR_ERR_ARG, "frame variant needs %u B of LDS per workgroup (limit %zu)",
+                        need.lds_counted(hi - lo), c->lds_limit);
         // hashing variants take the occupancy-bound kernel when eight
         // workgroups (eight wavefronts per SIMD) fit in the LDS
         v.occ = (v.mode == kFrameHash || v.mode == kFramePHash) && 8ull * (v.lds_total + 64u) <= c->lds_limit;
@@ -839,18 +878,21 @@ vr_status draw_impl(vr_ctx *c, const uint32_t *d_indices, uint64_t num_indices, 
     uint32_t lds = 0;
     bool stream = false;
     if (strategy != VR_NAIVE && strategy != VR_MULTI && !is_ballot(strategy)) {
-        lds = dedup_lds_layout(mode, r.max_idx, r.max_uniq, r.hash_bits, r.nt, r.max_uniq).total;
+        lds = dedup_lds_layout(mode, is_dynamic(strategy), r.max_idx, r.max_uniq, r.hash_bits, r.nt, r.max_uniq).total;
+        uint32_t counted = dedup_lds_counted(mode, r.max_idx, r.max_uniq, r.size_bits, r.size_nt, r.max_uniq);
+        if (!out->corners && 3 * counted > c->lds_limit)
+            counted = dedup_lds_counted(mode, r.max_idx, r.max_uniq, r.size_bits, r.size_nt, r.size_nt);
         // indexed outputs only: shaded vertices stream out when keeping them all
         // would leave room for fewer than three workgroups per CU
         if (!out->corners && 3 * lds > c->lds_limit) {
             stream = true;
-            lds = dedup_lds_layout(mode, r.max_idx, r.max_uniq, r.hash_bits, r.nt, r.nt).total;
+            lds = dedup_lds_layout(mode, is_dynamic(strategy), r.max_idx, r.max_uniq, r.hash_bits, r.nt, r.nt).total;
         }
-        if (lds > c->lds_limit)
+        if (std::max(counted, lds) > c->lds_limit)
             return fail(c, VR_ERR_ARG,
                         "LDS need %u B exceeds the %zu B limit (lower max_unique, batch_tris or hash_slots, or "
                         "request indexed outputs only)",
-                        lds, c->lds_limit);
+                        std::max(counted, lds), c->lds_limit);
     }
     unsigned char *fixed = nullptr;   // the static scratch array on this device (noalloc)
     if (noalloc) {
@@ -1230,7 +1272,7 @@ vr_status vr_frame_create(vr_ctx *c, const vr_draw *draws, uint32_t n, const vr_
     FrameNeeds need;
     for (uint32_t d = 0; d < n; ++d) {
         if (draws[d].shader >= ns) return fail(c, VR_ERR_ARG, "draw %u: shader %u out of range", d, draws[d].shader);
-        vr_status st = describe_draw(c, draws[d], shaders[draws[d].shader], d, desc[d], needs[d]);
+        vr_status st = describe_draw(c, draws[d], shaders[draws[d].shader], d, desc[d], needs[d], &c->d_words->err);
         if (st != VR_OK) return st;
         need.merge(needs[d]);
     }
@@ -1578,6 +1620,7 @@ vr_status server_launch(vr_server *s, uint32_t tick, const std::vector<uint64_t>
     vr_shader_params *hs = (vr_shader_params *)(S.host + L.sh);
     memset(S.host + L.words, 0, 256);
     unsigned long long *dcnt = (unsigned long long *)(S.dev + L.cnt);
+    CtxWords *dw = (CtxWords *)(S.dev + L.words);
     FrameNeeds need;
     std::vector<FrameNeeds> needs(n);
     for (uint32_t d = 0; d < n; ++d) {
@@ -1603,12 +1646,12 @@ vr_status server_launch(vr_server *s, uint32_t tick, const std::vector<uint64_t>
                 D.num_indices = 0;
             }
         }
-        if (describe_draw(c, D, hs[d], d, hd[d], needs[d]) != VR_OK) {
+        if (describe_draw(c, D, hs[d], d, hd[d], needs[d], &dw->err) != VR_OK) {
             if (j->status == VR_OK) j->status = VR_ERR_ARG;
             D.num_indices = 0;
             D.d_plan = nullptr;
             needs[d] = FrameNeeds();
-            if (describe_draw(c, D, hs[d], d, hd[d], needs[d]) != VR_OK) return VR_ERR_ARG;
+            if (describe_draw(c, D, hs[d], d, hd[d], needs[d], &dw->err) != VR_OK) return VR_ERR_ARG;
         }
         need.merge(needs[d]);
     }
@@ -1626,7 +1669,6 @@ vr_status server_launch(vr_server *s, uint32_t tick, const std::vector<uint64_t>
             return server_fail(s, VR_ERR_OOM, "tick aggregates: out of memory");
         }
     }
-    CtxWords *dw = (CtxWords *)(S.dev + L.words);
     FrameLaunch F{(const DrawDesc *)S.dev, (const uint32_t *)(S.dev + L.ord), n,
                   (const vr_shader_params *)(S.dev + L.sh), (uint32_t *)(S.dev + L.ubase),
                   (uint32_t *)(S.dev + L.sbase), S.agg, (unsigned long long *)(S.dev + L.dtot), vars.data(),
@@ -1879,9 +1921,9 @@ static vr_status server_submit_locked(vr_server *s, const vr_request *r, uint64_
     D.max_unique = R.nu;
     D.d_plan = M.idx;          // stands in for the plan during validation
     D.d_corners = (float *)s->arena;
-    if (describe_draw(s->ctx, D, r->shader, 0, X, need) != VR_OK)
+    if (describe_draw(s->ctx, D, r->shader, 0, X, need, nullptr) != VR_OK)
         return server_fail(s, VR_ERR_ARG, "%s", s->ctx->error.c_str());
-    if (need.lds_total(s->cfg.max_tick_draws) > s->ctx->lds_limit)
+    if (need.lds_counted(s->cfg.max_tick_draws) > s->ctx->lds_limit)
         return server_fail(s, VR_ERR_ARG, "the request needs more LDS than a tick allows");
     const uint64_t bytes = 144ull * r->num_tris;
     uint64_t t = 0;
