@@ -176,7 +176,12 @@ __global__ __launch_bounds__(kFrameNT) __attribute__((amdgpu_waves_per_eu(OCC ? 
     // registers (as kernel arguments do in a single draw) instead of taking
     // vector registers and vector loads.
     auto base_at = [&](uint32_t k) { return (uint32_t)__builtin_amdgcn_readfirstlane(s_base[k]); };
-    for (uint32_t c0 = base_at(0) + blockIdx.x * kChunk; c0 < U; c0 += G * kChunk) {
+    // each round of G chunks is dealt out in one contiguous run per XCD; the
+    // last, partial one in dispatch order, which spreads it over the XCDs
+    const uint32_t piece = xcd_piece(blockIdx.x, G);
+    for (uint32_t r0 = base_at(0); r0 < U; r0 += G * kChunk) {
+        const uint32_t c0 = r0 + (U - r0 >= G * kChunk ? piece : blockIdx.x) * kChunk;
+        if (c0 >= U) break;
         // the draw of unit c0: largest k with s_base[k] <= c0
         uint32_t a = 0, b = m;   // invariant: s_base[a] <= c0 < s_base[b]
         while (b - a > 1) {
