@@ -1226,21 +1226,35 @@ vr_status vr_walk_step(vr_ctx *c, const uint32_t *d_keys_in, uint32_t num_agents
     W.counters = (unsigned long long *)d_counters;
     W.total_inv = &c->d_words->total_inv;
     W.err = &c->d_words->err;
+    // moves listed by weight in LDS while they fit
+    const uint32_t list_bytes = num_moves <= kWalkListed ? 8 * num_moves : 0u;
     if (strategy == VR_NAIVE) {
         TimedRegion timed(c);
-        hipLaunchKernelGGL(k_walk_naive, dim3((num_agents + 255) / 256), dim3(256), 0, c->stream, W);
+        const dim3 grid_n((num_agents + 255) / 256);
+        if (list_bytes) hipLaunchKernelGGL(k_walk_naive<true>, grid_n, dim3(256), list_bytes, c->stream, W);
+        else hipLaunchKernelGGL(k_walk_naive<false>, grid_n, dim3(256), 0, c->stream, W);
         VR_HIP(c, hipGetLastError());
         return VR_OK;
     }
+    // few batches leave most of the chip idle: several workgroups per batch
+    // then share its cells (5,000 agents in 10 batches: 146 us with one
+    // workgroup each, 70 us with 16, before other changes brought that to 33).
+    // Not where a workgroup's moves could change the keys another one reads.
     const uint32_t nb = (num_agents + batch_agents - 1) / batch_agents;
-    vr_status st = ensure(c, c->agg, 8ull * nb);
+    const bool apart = d_keys_out + num_agents <= d_keys_in || d_keys_in + num_agents <= d_keys_out;
+    W.parts = !apart ? 1u : nb <= 64 ? 16u : nb <= 256 ? 4u : 1u;
+    const uint32_t groups = nb * W.parts;
+    vr_status st = ensure(c, c->agg, 8ull * groups);
     if (st != VR_OK) return st;
     W.agg = (unsigned long long *)c->agg.ptr;
     TimedRegion timed(c);
-    hipLaunchKernelGGL(k_walk_hash<kWalkThreads>, dim3(nb), dim3(kWalkThreads), 0, c->stream, W);
+    if (list_bytes)
+        hipLaunchKernelGGL((k_walk_hash<kWalkThreads, true>), dim3(groups), dim3(kWalkThreads), list_bytes, c->stream, W);
+    else
+        hipLaunchKernelGGL((k_walk_hash<kWalkThreads, false>), dim3(groups), dim3(kWalkThreads), 0, c->stream, W);
     timed.done();
-    const uint32_t fin = std::min<uint32_t>(64, std::max<uint32_t>(1, (nb + 2047) / 2048));
-    hipLaunchKernelGGL(k_finish, dim3(fin), dim3(256), 0, c->stream, (const uint32_t *)nullptr, nb, nb,
+    const uint32_t fin = std::min<uint32_t>(64, std::max<uint32_t>(1, (groups + 2047) / 2048));
+    hipLaunchKernelGGL(k_finish, dim3(fin), dim3(256), 0, c->stream, (const uint32_t *)nullptr, groups, groups,
                        (const unsigned long long *)W.agg, (unsigned long long *)nullptr, W.counters, W.total_inv);
     VR_HIP(c, hipGetLastError());
     return VR_OK;
