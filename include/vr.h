@@ -245,17 +245,18 @@ vr_status vr_process_draw_noalloc(vr_ctx *ctx, const uint32_t *d_indices, uint64
  * Streaming (Sections 4.2 and 5): index chunks are drawn as they arrive with
  * strategies that need no analysis of the index buffer (NAIVE, STATIC_*),
  * each into one of `slots` corner buffers of chunk_tris triangles (owned by
- * the stream), and a consumer on a second HIP stream runs triangle setup on
- * every finished buffer: the clip-space corners are divided by w and mapped
- * to a width x height viewport; each triangle gets its bounding box clamped
+ * the stream), and triangle setup consumes every triangle as its batch is
+ * written: the clip-space corners are divided by w and mapped to a width x
+ * height viewport; each triangle gets its bounding box clamped
  * to the viewport and its signed area, and is visible when every w > 0, the
  * area is positive (counter-clockwise) and the box is not empty (a corner at
  * w <= 0 gives an all-zero record).  Records land in d_records (caller-owned,
  * float[records_cap][8] = {xmin, ymin, xmax, ymax, area, flags, 0, 0}, flags
  * a uint32 with bit 0 = visible) at the triangle's position in the stream.
- * A buffer is drawn into again only after the consumer has finished it
- * (events), so memory stays bounded for any stream length.  Static batches
- * restart at every chunk.  A stream belongs to its context and must be
+ * The buffers are drawn into in turn, in the order of the context's stream,
+ * so memory stays bounded for any stream length; a destroyed stream leaves up
+ * to 256 MB of them to the context for the next one.  Static batches restart
+ * at every chunk.  A stream belongs to its context and must be
  * destroyed before it; push is not thread safe.  Errors: VR_ERR_ARG (slots outside 1..8,
  * chunk_tris outside 1..2^24, a dynamic strategy, a chunk above chunk_tris),
  * VR_ERR_CAPACITY (records_cap exceeded), draw errors as vr_process_draw.
@@ -266,7 +267,7 @@ vr_status vr_stream_create(vr_ctx *ctx, uint32_t slots, uint32_t chunk_tris, uin
 vr_status vr_stream_push(vr_stream *stream, const uint32_t *d_indices, uint64_t num_indices, const float *d_vertices,
                          uint32_t num_vertices, const vr_shader_params *shader, vr_strategy strategy,
                          uint32_t batch_tris);
-/* Waits for both stages; totals since creation: triangles pushed, visible
+/* Waits for the stream's work; totals since creation: triangles pushed, visible
  * triangles, vertex-shader invocations. */
 vr_status vr_stream_finish(vr_stream *stream, uint64_t *h_triangles, uint64_t *h_visible, uint64_t *h_invocations);
 void vr_stream_destroy(vr_stream *stream);

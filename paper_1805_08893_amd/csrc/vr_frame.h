@@ -124,16 +124,16 @@ __device__ __forceinline__ void frame_unit(ArgsPtr args, ShaderPtr shader, uint3
     const DrawArgs &A = *(const DrawArgs *)args;
     const vr_shader_params &sh = *(const vr_shader_params *)shader;
     if (MODE == kFrameSort) {
-        dedup_unit<kFrameNT, kSort, KIND, false, 8>(args, shader, local, nb, smem, agg);
+        dedup_unit<kFrameNT, kSort, KIND, kCorners, 8>(args, shader, local, nb, smem, agg);
     } else if (MODE == kFrameHash) {
-        dedup_unit<kFrameNT, kHash, KIND, false, 8>(args, shader, local, nb, smem, agg);
+        dedup_unit<kFrameNT, kHash, KIND, kCorners, 8>(args, shader, local, nb, smem, agg);
     } else if (MODE == kFramePHash) {
-        dedup_unit<kFrameNT, kPHash, KIND, false, 8>(args, shader, local, nb, smem, agg);
+        dedup_unit<kFrameNT, kPHash, KIND, kCorners, 8>(args, shader, local, nb, smem, agg);
     } else if (MODE == kFrameBallot) {
         const uint32_t w = threadIdx.x / kWave;
         const uint32_t b = 4 * local + w;
         unsigned char *mine = smem + w * ballot_stride;
-        if (b < nb) ballot_batch<KIND>(A, sh, b, nb, mine, agg);
+        if (b < nb) ballot_batch<KIND, kCorners>(A, sh, b, nb, mine, agg);
         __syncthreads();
     } else {
         const unsigned long long sum = naive_chunk<KIND>(A, sh, local, (f4 *)smem);

@@ -5,10 +5,13 @@
 #include <type_traits>
 
 #include "vr_device.h"
+#include "vr_stream.h"
 
 namespace vr {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
+// What a unit writes: per-corner vertices alone, any of a draw's outputs, or
+// per-corner vertices and a stream's triangle records.
+enum UnitOut { kCorners = 0, kAll = 1, kRecords = 2 };
 
 enum DedupMode { kSort = 0, kHash = 1, kPHash = 2 };
 
@@ -38,6 +41,7 @@ struct DrawArgs {
     uint32_t need_prefix;       // tris / verts / unit arrays requested
     uint32_t status_cap;        // look-back words available
     uint32_t stream_verts;      // no corners: shaded vertices stream out through an NT-row stage
+    SetupTarget setup;          // a stream's draw
 };
 
 // Draw arguments and shader parameters in constant memory (a launch's kernel
@@ -154,10 +158,11 @@ __device__ __forceinline__ void shade_to_lds(const DrawArgs &A, const vr_shader_
 // Assembly (Section 4.2): every corner of the unit's triangles receives its
 // shaded vertex.  The unit's corner rows are one contiguous span, so lane q
 // stores float4 q of the span: fully coalesced 16-byte stores.
-template <int NT, bool FULL, typename LocalT>
+template <int NT, int OUT, typename LocalT>
 __device__ __forceinline__ void write_unit(const DrawArgs &A, uint32_t t0, uint32_t ntri, const LocalT *s_local,
                                            const f4 *s_sv, uint32_t inv, uint32_t vbase, uint32_t unit,
                                            uint32_t tid, bool verts_written = false) {
+    constexpr bool FULL = OUT == kAll;
     const uint32_t ncorner = 3 * ntri;
     if (!FULL || A.corners) {
         // float4 q of the span is part q % 3 of corner q / 3.  Lane tid takes
@@ -294,6 +299,30 @@ __global__ __launch_bounds__(256) void k_naive(DrawArgs A, vr_shader_params sh) 
             A.counters[3] = 0;
         }
         atomicAdd(A.total_inv, n);
+    }
+}
+
+// A stream's naive draw: 85 triangles (255 corners) per workgroup, written and
+// set up from their shaded corners in LDS.
+constexpr uint32_t kNaiveTris = 85;
+
+template <int KIND>
+__global__ __launch_bounds__(256) void k_naive_records(DrawArgs A, vr_shader_params sh) {
+    __shared__ f4 s_sv[9 * kNaiveTris];
+    const uint32_t tid = threadIdx.x, t0 = xcd_piece(blockIdx.x, gridDim.x) * kNaiveTris;
+    const uint32_t ntri = min(kNaiveTris, A.T - t0);
+    if (tid < 3 * ntri) shade_to_lds<KIND>(A, sh, fetch_index(A, 3ull * t0 + tid), s_sv + 3 * tid);
+    __syncthreads();
+    f4 *dst = A.corners + 9ull * t0;
+    for (uint32_t q = tid; q < 9 * ntri; q += 256) __builtin_nontemporal_store(s_sv[q], dst + q);
+    if (tid < 2 * kWave) {   // the wavefronts that hold triangles, whole
+        bool vis = false;
+        if (tid < ntri) {
+            const f4 c[3] = {s_sv[9 * tid], s_sv[9 * tid + 3], s_sv[9 * tid + 6]};
+            vis = setup_triangle(A.setup, c, t0 + tid);
+        }
+        const uint32_t seen = (uint32_t)__popcll(ballot(vis));
+        if (lane_id() == 0) setup_totals(A.setup, 2 * blockIdx.x + tid / kWave, seen, tid == 0 ? 3 * ntri : 0u, ntri);
     }
 }
 
@@ -597,9 +626,8 @@ __device__ __forceinline__ void insert_rows(const DrawArgs &A, uint32_t *s_table
 //   phash - as hash, but a lane that fails `probes` linear probes hands its
 //           key to a wavefront-cooperative probe of 64 slots at a time.
 // Corner i of the unit is row i / NT of thread i % NT; a thread's rows stay
-// in registers from the index load to the local ids.  FULL units may have any
-// of the outputs; the others have corners only.  The sort takes at most
-// SORT_ROUNDS indices per thread.
+// in registers from the index load to the local ids.  OUT says what the unit
+// writes.  The sort takes at most SORT_ROUNDS indices per thread.
 //
 // A unit is a serial chain (index load, insertion, vertex gather, shading,
 // stores) between barriers, so its phases are kept few and their loads early:
@@ -610,9 +638,10 @@ __device__ __forceinline__ void insert_rows(const DrawArgs &A, uint32_t *s_table
 // wavefront and 53.3 us, sort 2,220 and 64.0 us, indexed phash 61.2 us; so
 // hash takes 941 and 51.7 us, sort 1,320 and 57.3 us, indexed phash 50.1 us.
 // ---------------------------------------------------------------------------
-template <int NT, int MODE, int KIND, bool FULL, uint32_t SORT_ROUNDS>
+template <int NT, int MODE, int KIND, int OUT, uint32_t SORT_ROUNDS>
 __device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint32_t u, uint32_t nb,
                                            unsigned char *smem, unsigned long long *agg) {
+    constexpr bool FULL = OUT == kAll;
     constexpr uint32_t NW = NT / kWave, kChunk = kRows * NT;
     const DrawArgs &A = *(const DrawArgs *)reread(args);
     // without corners, units whose unique vertices would not leave room for
@@ -930,8 +959,13 @@ __device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint3
         }
     }
     if (fits && (inv > 0 || t1 == t0))
-        write_unit<NT, FULL>(B, t0, t1 - t0, s_local, s_sv, inv, FULL ? s_vbase : 0u, u, tid, stream);
-    if (tid == 0) agg[u] = (1ull << 32) | inv;
+        write_unit<NT, OUT>(B, t0, t1 - t0, s_local, s_sv, inv, FULL ? s_vbase : 0u, u, tid, stream);
+    if (OUT == kRecords) {
+        const uint32_t seen = fits && inv > 0 ? setup_unit<NT>(B.setup, t0, t1 - t0, s_local, s_sv, tid) : 0u;
+        if (lane == 0) setup_totals(B.setup, u * NW + w, seen, tid == 0 ? inv : 0u, 1);
+    } else if (tid == 0) {
+        agg[u] = (1ull << 32) | inv;
+    }
     __syncthreads();   // the caller may reuse the LDS for the next unit
 }
 
@@ -956,8 +990,8 @@ struct DedupLaunch {
 // LDS lets that many workgroups reside, and then the extra wavefronts hide
 // more of a unit's serial latency; otherwise the bound would only add
 // spills.
-template <int NT, int MODE, int KIND, bool OCC, bool FULL>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC ? dedup_waves(MODE, FULL) : MODE == kSort ? 5 : 6))) void k_dedup(DedupLaunch) {
+template <int NT, int MODE, int KIND, bool OCC, int OUT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC ? dedup_waves(MODE, OUT == kAll) : MODE == kSort ? 5 : 6))) void k_dedup(DedupLaunch) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // the launch's only argument, at the start of the kernel-argument segment
     const VR_CONSTANT DedupLaunch *P = (const VR_CONSTANT DedupLaunch *)__builtin_amdgcn_kernarg_segment_ptr();
@@ -967,9 +1001,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC ? dedup_
     // units with prefix outputs wait for their predecessors: in dispatch order;
     // so are the units past the first of each workgroup, which are few and
     // would otherwise all fall to one XCD
-    uint64_t u = (uint64_t)P->base + (FULL ? blockIdx.x : xcd_piece(blockIdx.x, gridDim.x));
+    uint64_t u = (uint64_t)P->base + (OUT == kAll ? blockIdx.x : xcd_piece(blockIdx.x, gridDim.x));
     for (uint64_t next = (uint64_t)P->base + blockIdx.x; u < nb; u = next) {
-        dedup_unit<NT, MODE, KIND, FULL, OCC ? 3 : 8>(&P->A, &P->sh, (uint32_t)u, nb, smem, A.agg);
+        dedup_unit<NT, MODE, KIND, OUT, OCC ? 3 : 8>(&P->A, &P->sh, (uint32_t)u, nb, smem, A.agg);
         next += P->stride ? P->stride : nb;
     }
 }
@@ -1098,7 +1132,7 @@ __device__ __forceinline__ uint32_t ballot_round(const DrawArgs &A, uint32_t t0,
 // ballot_lds_bytes(batch_tris) bytes.  The batch's indices are loaded once,
 // up front; only wavefront-level synchronisation is used, so several
 // wavefronts of a workgroup can work on different batches.
-template <int KIND>
+template <int KIND, int OUT>
 __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_params &sh, uint32_t b, uint32_t nb,
                                              unsigned char *lds, unsigned long long *agg_out) {
     const uint32_t lane = lane_id();
@@ -1118,7 +1152,7 @@ __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_
     wave_sync_lds();
     uint32_t vbase = 0, ubase = b;
     RoundState st;
-    if (A.need_prefix) {
+    if (OUT == kAll && A.need_prefix) {
         // counting sweep: the batch's rounds and invocations, published
         // before any output so later batches can resolve their prefix
         uint32_t rounds = 0, inv = 0;
@@ -1132,18 +1166,23 @@ __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_
         vbase = __builtin_amdgcn_readfirstlane((uint32_t)ex);
         ubase = __builtin_amdgcn_readfirstlane((uint32_t)((ex >> 32) & 0x3FFFFFFFu));
     }
-    uint32_t r = 0, inv = 0;
+    uint32_t r = 0, inv = 0, seen = 0;
     for (uint32_t cur = t0; cur < t1; ++r) {
         const uint32_t end = ballot_round(A, t0, cur, t1, s_keys, pre, s_new, s_map, st);
         if (lane < st.fill) shade_raw_to_lds<KIND>(sh, st.va, st.vb, s_sv + 3 * lane);
         wave_sync_lds();
-        write_unit<64, true>(A, cur, end - cur, s_map, s_sv, st.fill, vbase, ubase + r, lane);
+        if (OUT == kRecords) seen += setup_unit<64>(A.setup, cur, end - cur, s_map, s_sv, lane);
+        write_unit<64, OUT>(A, cur, end - cur, s_map, s_sv, st.fill, vbase, ubase + r, lane);
         wave_sync_lds();
         vbase += st.fill;
         inv += st.fill;
         cur = end;
     }
-    if (A.unit_offsets && b + 1 == nb && lane == 0) A.unit_offsets[ubase + r] = A.T;
+    if (OUT == kRecords) {
+        if (lane == 0) setup_totals(A.setup, b, seen, inv, r);
+        return;
+    }
+    if (OUT == kAll && A.unit_offsets && b + 1 == nb && lane == 0) A.unit_offsets[ubase + r] = A.T;
     if (lane == 0) agg_out[b] = ((unsigned long long)r << 32) | inv;
 }
 
@@ -1152,7 +1191,7 @@ __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_
 // than four and eight, and about as fast as one.
 constexpr uint32_t kBallotWaves = 2;
 
-template <int KIND>
+template <int KIND, int OUT>
 __global__ __launch_bounds__(kBallotWaves * 64) void k_ballot(DrawArgs A, vr_shader_params sh, uint32_t stride) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     clear_counters(A);
@@ -1164,7 +1203,7 @@ __global__ __launch_bounds__(kBallotWaves * 64) void k_ballot(DrawArgs A, vr_sha
     if (blockIdx.x >= pieces) return;
     const uint32_t b = (A.need_prefix ? blockIdx.x : xcd_piece(blockIdx.x, pieces)) * kBallotWaves + w;
     if (b >= nb) return;   // only wavefront-level synchronisation follows
-    ballot_batch<KIND>(A, sh, b, nb, smem + w * stride, A.agg);
+    ballot_batch<KIND, OUT>(A, sh, b, nb, smem + w * stride, A.agg);
 }
 
 }  // namespace vr

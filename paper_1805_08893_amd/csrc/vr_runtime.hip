@@ -38,6 +38,14 @@ struct CtxWords {
     uint32_t err;
     uint32_t plan_fail;   // epoch of the last planning call whose aligned chain failed
     unsigned long long total_inv;
+    unsigned long long pad[6];
+    unsigned long long spread[kSpread][kSpreadWords];   // streams' part of the total (word 0 of each row)
+
+    unsigned long long invocations() const {
+        unsigned long long t = total_inv;
+        for (const auto &row : spread) t += row[0];
+        return t;
+    }
 };
 
 struct Scratch {
@@ -57,6 +65,8 @@ struct vr_ctx {
     Scratch status, agg, plan, plan_work, tune, shaded;   // shaded: MULTI's vertex pass
     Scratch plan_status;                                   // the planner's epoch-tagged look-back words
     Scratch selftest;                                      // vr_math_selftest's counter
+    int live_streams = 0;         // vr_stream objects
+    Scratch ring;                 // a destroyed stream's buffers, for the next one (at most kRingKept bytes)
     uint32_t host_err = 0;   // data error found on the host, reported by vr_sync
     uint32_t plan_epoch = 0;  // numbers planning calls (0 is never used)
     bool timing = false;
@@ -269,33 +279,36 @@ vr_status check_args(vr_ctx *c, uint64_t num_indices, uint32_t num_vertices, con
     return VR_OK;
 }
 
+// Draws with corners and counters only take kernels compiled without the
+// other outputs.
+bool corners_only(const DrawArgs &A) { return A.corners && !A.need_prefix && !A.local_idx; }
+
 // A static draw's units are exactly known.  A dynamic draw has at least
 // ceil(T / N_pmax) units (exactly that many when every batch is full) and at
 // most the host-side bound.  The launch has one workgroup per unit of the
 // fewest; without prefix outputs (units in any order) the same workgroups
 // take the rest grid-stride, else a second launch has one workgroup per
 // possible further unit.
-template <int NT, int MODE, int KIND, bool OCC, bool FULL>
+template <int NT, int MODE, int KIND, bool OCC, int OUT>
 void launch_dedup_as(vr_ctx *c, const DrawArgs &A, const vr_shader_params &sh, uint32_t lds, uint64_t units) {
     uint64_t first = units;
     if (A.plan) first = std::min<uint64_t>(units, (A.T + A.batch_tris - 1) / A.batch_tris);
     const bool stride = A.plan && !A.need_prefix && first > 0 && units > first;
     if (first)
-        hipLaunchKernelGGL((k_dedup<NT, MODE, KIND, OCC, FULL>), dim3((uint32_t)first), dim3(NT), lds, c->stream,
+        hipLaunchKernelGGL((k_dedup<NT, MODE, KIND, OCC, OUT>), dim3((uint32_t)first), dim3(NT), lds, c->stream,
                            (DedupLaunch{A, sh, 0u, stride ? (uint32_t)first : 0u}));
     if (units > first && !stride)
-        hipLaunchKernelGGL((k_dedup<NT, MODE, KIND, OCC, FULL>), dim3((uint32_t)(units - first)), dim3(NT), lds,
+        hipLaunchKernelGGL((k_dedup<NT, MODE, KIND, OCC, OUT>), dim3((uint32_t)(units - first)), dim3(NT), lds,
                            c->stream, (DedupLaunch{A, sh, (uint32_t)first, 0u}));
 }
 
-// Draws with corners and counters only take kernels compiled without the
-// other outputs.
-bool corners_only(const DrawArgs &A) { return A.corners && !A.need_prefix && !A.local_idx; }
-
 template <int NT, int MODE, int KIND, bool OCC>
 void launch_dedup(vr_ctx *c, const DrawArgs &A, const vr_shader_params &sh, uint32_t lds, uint64_t units) {
-    if (corners_only(A)) launch_dedup_as<NT, MODE, KIND, OCC, false>(c, A, sh, lds, units);
-    else launch_dedup_as<NT, MODE, KIND, OCC, true>(c, A, sh, lds, units);
+    // a stream's static draws: 64, 128 or 256 threads
+    constexpr bool streams = MODE != kPHash && NT <= 256;
+    if (streams && A.setup.records) launch_dedup_as<NT, MODE, KIND, OCC, streams ? kRecords : kCorners>(c, A, sh, lds, units);
+    else if (corners_only(A)) launch_dedup_as<NT, MODE, KIND, OCC, kCorners>(c, A, sh, lds, units);
+    else launch_dedup_as<NT, MODE, KIND, OCC, kAll>(c, A, sh, lds, units);
 }
 
 // Whether a dedup launch of nt threads and lds bytes per workgroup takes the
@@ -337,12 +350,19 @@ void dispatch_kind(vr_ctx *c, uint32_t kind, uint32_t nt, const DrawArgs &A, con
 
 template <int KIND>
 void launch_ballot(vr_ctx *c, const DrawArgs &A, const vr_shader_params &sh, uint32_t stride, uint64_t batches) {
-    hipLaunchKernelGGL(k_ballot<KIND>, dim3((uint32_t)((batches + kBallotWaves - 1) / kBallotWaves)),
-                       dim3(kBallotWaves * 64), kBallotWaves * stride, c->stream, A, sh, stride);
+    const dim3 grid((uint32_t)((batches + kBallotWaves - 1) / kBallotWaves)), block(kBallotWaves * 64);
+    const uint32_t lds = kBallotWaves * stride;
+    if (A.setup.records) hipLaunchKernelGGL((k_ballot<KIND, kRecords>), grid, block, lds, c->stream, A, sh, stride);
+    else if (corners_only(A)) hipLaunchKernelGGL((k_ballot<KIND, kCorners>), grid, block, lds, c->stream, A, sh, stride);
+    else hipLaunchKernelGGL((k_ballot<KIND, kAll>), grid, block, lds, c->stream, A, sh, stride);
 }
 
 template <int KIND>
 void launch_naive(vr_ctx *c, const DrawArgs &A, const vr_shader_params &sh) {
+    if (A.setup.records) {
+        hipLaunchKernelGGL(k_naive_records<KIND>, dim3((A.T + kNaiveTris - 1) / kNaiveTris), dim3(256), 0, c->stream, A, sh);
+        return;
+    }
     const uint64_t blocks = (3ull * A.T + 255) / 256;
     hipLaunchKernelGGL(k_naive<KIND>, dim3((uint32_t)blocks), dim3(256), 0, c->stream, A, sh);
 }
@@ -809,7 +829,8 @@ void vr_destroy(vr_ctx *c) {
     if (!c) return;
     DeviceGuard g(c->device);
     (void)hipStreamSynchronize(c->stream);
-    for (Scratch *s : {&c->status, &c->agg, &c->plan, &c->plan_work, &c->tune, &c->shaded, &c->plan_status})
+    for (Scratch *s : {&c->status, &c->agg, &c->plan, &c->plan_work, &c->tune, &c->shaded, &c->plan_status,
+                       &c->selftest, &c->ring})
         if (s->ptr) (void)hipFree(s->ptr);
     for (auto &pr : c->ev_pool) {
         (void)hipEventDestroy(pr.first);
@@ -821,7 +842,17 @@ void vr_destroy(vr_ctx *c) {
 
 vr_status vr_set_stream(vr_ctx *c, void *hip_stream) {
     if (!c) return VR_ERR_ARG;
-    c->stream = (hipStream_t)hip_stream;
+    const hipStream_t to = (hipStream_t)hip_stream;
+    if (c->live_streams && to != c->stream) {   // the chunks a stream pushed so far precede its next ones
+        DeviceGuard g(c->device);
+        hipEvent_t e = nullptr;
+        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess) {
+            if (hipEventRecord(e, c->stream) == hipSuccess) (void)hipStreamWaitEvent(to, e, 0);
+            (void)hipEventDestroy(e);
+        }
+        (void)hipGetLastError();   // a stream that is gone has nothing to wait for
+    }
+    c->stream = to;
     return VR_OK;
 }
 
@@ -855,12 +886,14 @@ vr_status vr_plan_dynamic(vr_ctx *c, const uint32_t *d_indices, uint64_t num_ind
 
 namespace {
 
-// One draw (vr_process_draw).  With noalloc the per-batch aggregates and
+// One draw (vr_process_draw), or one chunk of a stream (setup given: a static
+// or naive draw of corners whose kernels write the records and totals too).
+// With noalloc the per-batch aggregates and
 // look-back words come from the static `scratch` array instead of context
 // scratch, a dynamic draw must bring its plan, and nothing is allocated.
 vr_status draw_impl(vr_ctx *c, const uint32_t *d_indices, uint64_t num_indices, const float *d_vertices,
                     uint32_t num_vertices, const vr_shader_params *shader, vr_strategy strategy, uint32_t batch_tris,
-                    const vr_opts *opts, const vr_outputs *out, bool noalloc) {
+                    const vr_opts *opts, const vr_outputs *out, bool noalloc, const SetupTarget *setup = nullptr) {
     if (!c) return VR_ERR_ARG;
     Resolved r;
     vr_status st = check_args(c, num_indices, num_vertices, shader, strategy, batch_tris, opts, out, &r);
@@ -944,6 +977,7 @@ vr_status draw_impl(vr_ctx *c, const uint32_t *d_indices, uint64_t num_indices, 
     A.max_uniq = r.max_uniq;
     A.need_prefix = (out->tris || out->verts || out->unit_offsets || out->unit_invocations) ? 1u : 0u;
     A.stream_verts = stream ? 1u : 0u;
+    if (setup) A.setup = *setup;
 
     const vr_shader_params &sh = *shader;
     if (strategy == VR_MULTI) {
@@ -991,7 +1025,9 @@ vr_status draw_impl(vr_ctx *c, const uint32_t *d_indices, uint64_t num_indices, 
     }
     // one workgroup per batch; a dynamic launch covers the batch bound and
     // workgroups past the plan's count return at once
-    if (noalloc) {
+    if (setup) {
+        A.status_cap = (uint32_t)nb_bound;
+    } else if (noalloc) {
         A.agg = (unsigned long long *)fixed;
         A.status = A.need_prefix ? (unsigned long long *)(fixed + 8ull * VR_NOALLOC_MAX_BATCHES) : nullptr;
         A.status_cap = (uint32_t)nb_bound;
@@ -1021,6 +1057,10 @@ vr_status draw_impl(vr_ctx *c, const uint32_t *d_indices, uint64_t num_indices, 
         else dispatch_kind<kPHash>(c, sh.kind, r.nt, A, sh, lds, nb_bound);
     }
     timed.done();
+    if (setup) {   // the units added to the totals themselves
+        VR_HIP(c, hipGetLastError());
+        return VR_OK;
+    }
     const uint32_t fin = (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, (nb_bound + 2047) / 2048));
     hipLaunchKernelGGL(k_finish, dim3(fin), dim3(256), 0, c->stream, A.plan, A.num_batches, A.status_cap,
                        (const unsigned long long *)A.agg, A.status, A.counters, A.total_inv);
@@ -1048,35 +1088,24 @@ vr_status vr_process_draw_noalloc(vr_ctx *c, const uint32_t *d_indices, uint64_t
 }
 
 // ---------------------------------------------------------------------------
-// Streams: chunks drawn into a ring of corner slots, consumed by triangle
-// setup on a second HIP stream; events order each slot's reuse.
+// Streams: chunks drawn into a ring of corner slots; each draw's kernel runs
+// triangle setup on its units (vr_stream.h), and the context's stream orders
+// the reuse of a slot.
 // ---------------------------------------------------------------------------
 struct vr_stream {
     vr_ctx *c = nullptr;
-    hipStream_t cons = nullptr;
     uint32_t slots = 0, chunk_tris = 0, width = 0, height = 0;
     f4 *records = nullptr;
     uint64_t records_cap = 0;
-    unsigned char *mem = nullptr;
+    Scratch mem;                              // the slots, then the totals
     size_t slot_bytes = 0;
-    unsigned long long *totals = nullptr;   // {visible, invocations, units, 0}
-    std::vector<hipEvent_t> produced, consumed;
-    std::vector<bool> used;
+    unsigned long long *totals = nullptr;     // [kSpread][kSpreadWords]
     uint64_t pushed = 0, next = 0;
 };
 
 namespace {
-f4 *stream_corners(vr_stream *s, uint32_t k) { return (f4 *)(s->mem + k * s->slot_bytes); }
-unsigned long long *stream_counters(vr_stream *s, uint32_t k) {
-    return (unsigned long long *)(s->mem + k * s->slot_bytes + s->slot_bytes - 256);
-}
-void stream_release(vr_stream *s) {
-    if (s->cons) (void)hipStreamSynchronize(s->cons);
-    for (hipEvent_t e : s->produced) (void)hipEventDestroy(e);
-    for (hipEvent_t e : s->consumed) (void)hipEventDestroy(e);
-    if (s->cons) (void)hipStreamDestroy(s->cons);
-    if (s->mem) (void)hipFree(s->mem);
-}
+constexpr size_t kTotalsBytes = sizeof(unsigned long long) * kSpread * kSpreadWords;
+constexpr size_t kRingKept = 256u << 20;
 }  // namespace
 
 vr_status vr_stream_create(vr_ctx *c, uint32_t slots, uint32_t chunk_tris, uint32_t width, uint32_t height,
@@ -1090,6 +1119,15 @@ vr_status vr_stream_create(vr_ctx *c, uint32_t slots, uint32_t chunk_tris, uint3
     if (records_cap && (!d_records || ((uintptr_t)d_records & 15)))
         return fail(c, VR_ERR_ARG, "records must be a 16-byte aligned device buffer");
     DeviceGuard g(c->device);
+    const size_t slot_bytes = (144ull * chunk_tris + 255) & ~(size_t)255, bytes = slot_bytes * slots + kTotalsBytes;
+    Scratch mem;
+    if (c->ring.bytes >= bytes) {   // the buffers a destroyed stream left; its work precedes this one's
+        mem = c->ring;
+        c->ring = Scratch();
+    } else {
+        if (hipMalloc(&mem.ptr, bytes) != hipSuccess) return fail(c, VR_ERR_OOM, "stream slots: out of memory");
+        mem.bytes = bytes;
+    }
     vr_stream *s = new vr_stream;
     s->c = c;
     s->slots = slots;
@@ -1098,36 +1136,16 @@ vr_status vr_stream_create(vr_ctx *c, uint32_t slots, uint32_t chunk_tris, uint3
     s->height = height;
     s->records = (f4 *)d_records;
     s->records_cap = records_cap;
-    s->slot_bytes = ((144ull * chunk_tris + 255) & ~(size_t)255) + 256;   // corners, then the draw's counters
-    vr_status st = VR_OK;
-    if (hipMalloc((void **)&s->mem, s->slot_bytes * slots + 256) != hipSuccess) {
-        s->mem = nullptr;
-        st = fail(c, VR_ERR_OOM, "stream slots: out of memory");
-    } else if (hipStreamCreateWithFlags(&s->cons, hipStreamNonBlocking) != hipSuccess) {
-        s->cons = nullptr;
-        st = fail(c, VR_ERR_DEVICE, "stream: cannot create the consumer stream");
-    }
-    for (uint32_t k = 0; st == VR_OK && k < slots; ++k) {
-        hipEvent_t a = nullptr, b = nullptr;
-        if (hipEventCreateWithFlags(&a, hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&b, hipEventDisableTiming) != hipSuccess) {
-            if (a) (void)hipEventDestroy(a);
-            st = fail(c, VR_ERR_DEVICE, "stream: cannot create events");
-            break;
-        }
-        s->produced.push_back(a);
-        s->consumed.push_back(b);
-    }
-    if (st == VR_OK) {
-        s->totals = (unsigned long long *)(s->mem + s->slot_bytes * slots);
-        if (hipMemsetAsync(s->totals, 0, 32, s->cons) != hipSuccess) st = fail(c, VR_ERR_DEVICE, "stream: memset");
-    }
-    if (st != VR_OK) {
-        stream_release(s);
+    s->mem = mem;
+    s->slot_bytes = slot_bytes;
+    s->totals = (unsigned long long *)((unsigned char *)mem.ptr + slot_bytes * slots);
+    hipLaunchKernelGGL(k_fill_u64, dim3(2), dim3(256), 0, c->stream, s->totals, (uint64_t)kSpread * kSpreadWords, 0ull);
+    if (hipGetLastError() != hipSuccess) {
+        (void)hipFree(mem.ptr);
         delete s;
-        return st;
+        return fail(c, VR_ERR_DEVICE, "stream: clearing the totals");
     }
-    s->used.assign(slots, false);
+    ++c->live_streams;
     *out = s;
     return VR_OK;
 }
@@ -1147,24 +1165,12 @@ vr_status vr_stream_push(vr_stream *s, const uint32_t *d_indices, uint64_t num_i
     if (s->pushed + T > s->records_cap)
         return fail(c, VR_ERR_CAPACITY, "records_cap %llu below %llu triangles", (unsigned long long)s->records_cap,
                     (unsigned long long)(s->pushed + T));
-    DeviceGuard g(c->device);
-    const uint32_t k = (uint32_t)(s->next % s->slots);
-    if (s->used[k]) VR_HIP(c, hipStreamWaitEvent(c->stream, s->consumed[k], 0));   // the consumer is done with it
     vr_outputs out{};
-    out.corners = (float *)stream_corners(s, k);
-    out.counters = (uint64_t *)stream_counters(s, k);
-    vr_status st = vr_process_draw(c, d_indices, num_indices, d_vertices, num_vertices, shader, strategy, batch_tris,
-                                   nullptr, &out);
+    out.corners = (float *)((unsigned char *)s->mem.ptr + s->next % s->slots * s->slot_bytes);
+    const SetupTarget setup{s->records + 2 * s->pushed, s->width, s->height, s->totals, c->d_words->spread[0]};
+    vr_status st = draw_impl(c, d_indices, num_indices, d_vertices, num_vertices, shader, strategy, batch_tris, nullptr,
+                             &out, false, &setup);
     if (st != VR_OK) return st;
-    VR_HIP(c, hipEventRecord(s->produced[k], c->stream));
-    VR_HIP(c, hipStreamWaitEvent(s->cons, s->produced[k], 0));
-    if (T)
-        hipLaunchKernelGGL(k_setup, dim3((uint32_t)((T + 255) / 256)), dim3(256), 0, s->cons,
-                           (const f4 *)stream_corners(s, k), (uint32_t)T, s->width, s->height,
-                           s->records + 2 * s->pushed, (const unsigned long long *)stream_counters(s, k), s->totals);
-    VR_HIP(c, hipGetLastError());
-    VR_HIP(c, hipEventRecord(s->consumed[k], s->cons));
-    s->used[k] = true;
     ++s->next;
     s->pushed += T;
     return VR_OK;
@@ -1174,21 +1180,29 @@ vr_status vr_stream_finish(vr_stream *s, uint64_t *h_triangles, uint64_t *h_visi
     if (!s) return VR_ERR_ARG;
     vr_ctx *c = s->c;
     DeviceGuard g(c->device);
+    unsigned long long t[kSpread][kSpreadWords];
     VR_HIP(c, hipStreamSynchronize(c->stream));
-    VR_HIP(c, hipStreamSynchronize(s->cons));
-    unsigned long long t[4] = {0, 0, 0, 0};
     VR_HIP(c, hipMemcpy(t, s->totals, sizeof t, hipMemcpyDeviceToHost));
+    unsigned long long visible = 0, inv = 0;
+    for (const auto &row : t) {
+        visible += row[0];
+        inv += row[1];
+    }
     if (h_triangles) *h_triangles = s->pushed;
-    if (h_visible) *h_visible = t[0];
-    if (h_invocations) *h_invocations = t[1];
+    if (h_visible) *h_visible = visible;
+    if (h_invocations) *h_invocations = inv;
     return VR_OK;
 }
 
 void vr_stream_destroy(vr_stream *s) {
     if (!s) return;
-    DeviceGuard g(s->c->device);
-    (void)hipStreamSynchronize(s->c->stream);
-    stream_release(s);
+    vr_ctx *c = s->c;
+    DeviceGuard g(c->device);
+    (void)hipStreamSynchronize(c->stream);
+    --c->live_streams;
+    // the context keeps one set of buffers for the next stream
+    if (s->mem.bytes <= kRingKept && s->mem.bytes > c->ring.bytes) std::swap(s->mem, c->ring);
+    if (s->mem.ptr) (void)hipFree(s->mem.ptr);
     delete s;
 }
 
@@ -1267,7 +1281,7 @@ vr_status vr_sync(vr_ctx *c, uint64_t *h_invocations) {
     CtxWords w{};
     VR_HIP(c, hipMemcpy(&w, c->d_words, sizeof w, hipMemcpyDeviceToHost));
     VR_HIP(c, hipMemset(c->d_words, 0, sizeof w));
-    if (h_invocations) *h_invocations = w.total_inv;
+    if (h_invocations) *h_invocations = w.invocations();
     uint32_t e = c->host_err ? c->host_err : w.err;
     c->host_err = 0;
     if (e == VR_ERR_INDEX_RANGE) return fail(c, VR_ERR_INDEX_RANGE, "an index is >= num_vertices");
