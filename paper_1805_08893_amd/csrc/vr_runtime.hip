@@ -444,8 +444,10 @@ template <uint32_t TMC>
 void launch_plan_first(vr_ctx *c, const PlanArgs &P, uint32_t K, uint32_t *d_plan) {
     using W = NextClass<TMC>;
     hipLaunchKernelGGL(k_plan_check<TMC>, dim3(K), dim3(CheckClass<TMC>::threads), 0, c->stream, P, d_plan);
-    hipLaunchKernelGGL(k_plan_next<TMC>, dim3((P.T + W::starts - 1) / W::starts), dim3(W::threads), W::lds,
-                       c->stream, P);
+    // at most eight workgroups per CU (four rounds of the two that reside), so
+    // that those of an aligned stream leave quickly (8.4M triangles: 52 -> 48 us)
+    const uint32_t blocks = std::min<uint32_t>((P.T + W::starts - 1) / W::starts, 8u * (uint32_t)std::max(1, c->num_cus));
+    hipLaunchKernelGGL(k_plan_next<TMC>, dim3(blocks), dim3(W::threads), W::lds, c->stream, P);
 }
 
 // Builds the plan of a dynamic draw on the context's stream (see vr_plan.h).
