@@ -1009,12 +1009,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC ? dedup_
 }
 
 // ---------------------------------------------------------------------------
-// Wave64 ballot rounds (Algorithm 1 on a 64-lane wavefront).  One wavefront
-// owns a batch and cuts it into rounds: it fetches 21 whole triangles (63
-// indices, one per lane) at a time and resolves them one distinct value at
-// a time: the lowest unresolved lane's index is broadcast (readlane), every
-// lane holding the same index is resolved together (ballot), and if no lane
-// holds it yet the lowest free lane takes it.  The first triangle that would
+// Wave64 rounds (Algorithm 1 on a 64-lane wavefront).  One wavefront owns a
+// batch and cuts it into rounds: it takes 21 whole triangles (63 indices, one
+// per lane) at a time, finds the lanes that hold an index the round has not
+// met (a small table in the wavefront's LDS brings equal indices together, the
+// lowest lane of each counts as its first), and a ballot of those lanes gives
+// each the next free lane, which will shade it.  The first triangle that would
 // need a 65th lane ends the round; lanes taken by rejected triangles are
 // released, so a round shades exactly its distinct indices.
 // ---------------------------------------------------------------------------
@@ -1037,67 +1037,62 @@ __host__ __device__ inline uint32_t ballot_lds_bytes(uint32_t batch_tris) {
 
 // Processes one round starting at triangle `cur` of the batch starting at
 // t0; returns the round's end.  The batch's first `pre` indices are in
-// s_keys; s_new is the wavefront's hand-over area.  When s_map is not NULL
-// it receives each corner's lane (local id).
+// s_keys; s_new is the wavefront's hand-over area, s_table kRoundSlots index
+// words and as many position words (the space of the round's shaded
+// vertices).  When s_map is not NULL it receives each corner's lane (local id).
 //
-// A group of 21 triangles is resolved by votes, one per distinct value: the
-// lowest unresolved lane broadcasts its index, and ballots give the lanes
-// holding it (whose first occurrence is that lane) and the lane that already
-// owns it.  Values no lane owns then get the next free lanes in the order of
-// their first lanes (a popcount of the first-occurrence mask below), and the
-// first lane hands the value to the lane of its slot through LDS.  This is
-// the sequential assignment of Algorithm 1, with the slot bookkeeping taken
-// out of the per-value loop (the scalar unit, shared by a CU's wavefronts,
-// bounds this loop).
+// Within a group equal indices meet in one slot of s_table; the smallest
+// position that reached the slot is the index's first occurrence, and its
+// lane then leaves the lane number there (never above the position, so later
+// positions change neither).  Resolving a group by one vote per distinct index
+// instead (broadcast, compare, ballot, about 14 instructions each in one
+// dependent chain) took 1,639 vector and 906 scalar instructions per batch of
+// 64 triangles and 63.7 us for the icosphere's 20,480 batches (Phong-8); the
+// table's few LDS round trips take 1,070 and 581, and 53.3 us.
+constexpr uint32_t kRoundBits = 8, kRoundSlots = 1u << kRoundBits;   // at most 64 + 63 indices at once
+
 __device__ __forceinline__ uint32_t ballot_round(const DrawArgs &A, uint32_t t0, uint32_t cur, uint32_t t1,
                                                  const uint32_t *s_keys, uint32_t pre, uint32_t *s_new,
-                                                 uint8_t *s_map, RoundState &st) {
+                                                 uint32_t *s_table, uint8_t *s_map, RoundState &st) {
+    static_assert(8 * kRoundSlots <= 64 * 48, "the table fits the shaded vertices' space");
     const uint32_t lane = lane_id();
     uint32_t my_id = kEmpty, my_intro = kEmpty, fill = 0, done = 0;
     f4 va = {}, vb = {};
+    uint32_t *s_first = s_table + kRoundSlots;
+#pragma unroll
+    for (uint32_t q = 0; q < 2 * kRoundSlots / 256; ++q)
+        ((uint4 *)s_table)[q * kWave + lane] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
+    wave_sync_lds();
     for (;;) {
         const uint32_t gt = min(21u, t1 - cur);
         const uint32_t nc = 3 * gt;
         const bool act = lane < nc;
         const uint32_t pos = __umul24(3u, cur - t0) + lane;   // cur - t0 < 2^24 (a batch)
         const uint32_t k = act ? (pos < pre ? s_keys[pos] : fetch_index(A, 3ull * cur + lane)) : kEmpty;
-        // one vote per distinct value, lowest unresolved lane first: that
-        // lane is the value's first occurrence in the group
-        uint64_t pend = ballot(act);
-        uint32_t first = lane, owner = kEmpty;
-        if (fill == 0) {   // nothing owned yet in this round
-            while (pend) {
-                const uint32_t pick = (uint32_t)__builtin_ctzll(pend);
-                const uint32_t cv = __builtin_amdgcn_readlane(k, pick);
-                const uint64_t same = ballot(k == cv);
-                first = __builtin_amdgcn_inverse_ballot_w64(same) ? pick : first;
-                pend &= ~same;
-            }
-        } else {
-            while (pend) {
-                const uint32_t pick = (uint32_t)__builtin_ctzll(pend);
-                const uint32_t cv = __builtin_amdgcn_readlane(k, pick);
-                const uint64_t same = ballot(k == cv);
-                // the owning lane, or lane 63 when none owns it (checked below)
-                const uint32_t ol = (uint32_t)__builtin_ctzll(ballot(my_id == cv) | (1ull << 63));
-                const bool in = __builtin_amdgcn_inverse_ballot_w64(same);
-                first = in ? pick : first;
-                owner = in ? ol : owner;
-                pend &= ~same;
-            }
-            // a candidate owner counts only if it holds the lane's index
-            const uint32_t held = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(owner << 2), (int)my_id);
-            if (!act || held != k) owner = kEmpty;
+        uint32_t at = hash_slot(k, kRoundBits);
+        for (bool todo = act; todo;) {   // linear probing; the table is at most half full
+            const uint32_t prev = atomicCAS(&s_table[at], kEmpty, k);
+            todo = prev != kEmpty && prev != k;
+            if (todo) at = (at + 1) & (kRoundSlots - 1);
         }
-        // first occurrences of values no lane owns yet
-        const uint64_t fresh = ballot(act && owner == kEmpty && first == lane);
-        const uint32_t slot = owner != kEmpty ? owner
-                                              : fill + (uint32_t)__popcll(fresh & ((1ull << first) - 1ull));
-        if (act && owner == kEmpty && first == lane && slot < (uint32_t)kWave) {
-            s_new[slot] = k;
-            s_new[kWave + slot] = done + lane;
+        const uint32_t mine = done + lane;   // position in the round
+        if (act) atomicMin(&s_first[at], mine);
+        wave_sync_lds();
+        const bool first = act && s_first[at] == mine;
+        // first occurrences of indices no lane owns yet
+        const uint64_t fresh = ballot(first);
+        const uint32_t next = fill + __builtin_amdgcn_mbcnt_hi((uint32_t)(fresh >> 32),
+                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)fresh, 0u));
+        wave_sync_lds();
+        if (first) {
+            s_first[at] = next;
+            if (next < (uint32_t)kWave) {
+                s_new[next] = k;
+                s_new[kWave + next] = mine;
+            }
         }
         wave_sync_lds();
+        const uint32_t slot = act ? s_first[at] : 0u;
         const uint32_t f = fill + (uint32_t)__popcll(fresh);
         if (lane >= fill && lane < f) {
             my_id = s_new[lane];
@@ -1157,7 +1152,7 @@ __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_
         // before any output so later batches can resolve their prefix
         uint32_t rounds = 0, inv = 0;
         for (uint32_t cur = t0; cur < t1; ++rounds) {
-            cur = ballot_round(A, t0, cur, t1, s_keys, pre, s_new, nullptr, st);
+            cur = ballot_round(A, t0, cur, t1, s_keys, pre, s_new, (uint32_t *)s_sv, nullptr, st);
             inv += st.fill;
         }
         const uint64_t agg = ((uint64_t)rounds << 32) | inv;
@@ -1168,7 +1163,7 @@ __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_
     }
     uint32_t r = 0, inv = 0, seen = 0;
     for (uint32_t cur = t0; cur < t1; ++r) {
-        const uint32_t end = ballot_round(A, t0, cur, t1, s_keys, pre, s_new, s_map, st);
+        const uint32_t end = ballot_round(A, t0, cur, t1, s_keys, pre, s_new, (uint32_t *)s_sv, s_map, st);
         if (lane < st.fill) shade_raw_to_lds<KIND>(sh, st.va, st.vb, s_sv + 3 * lane);
         wave_sync_lds();
         if (OUT == kRecords) seen += setup_unit<64>(A.setup, cur, end - cur, s_map, s_sv, lane);
