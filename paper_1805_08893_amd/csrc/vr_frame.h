@@ -124,16 +124,16 @@ __device__ __forceinline__ void frame_unit(ArgsPtr args, ShaderPtr shader, uint3
     const DrawArgs &A = *(const DrawArgs *)args;
     const vr_shader_params &sh = *(const vr_shader_params *)shader;
     if (MODE == kFrameSort) {
-        dedup_unit<kFrameNT, kSort, KIND, kCorners, 8>(args, shader, local, nb, smem, agg);
+        dedup_unit<kFrameNT, kSort, KIND, kCorners, 8, false>(args, shader, local, nb, smem, agg);
     } else if (MODE == kFrameHash) {
-        dedup_unit<kFrameNT, kHash, KIND, kCorners, 8>(args, shader, local, nb, smem, agg);
+        dedup_unit<kFrameNT, kHash, KIND, kCorners, 8, false>(args, shader, local, nb, smem, agg);
     } else if (MODE == kFramePHash) {
-        dedup_unit<kFrameNT, kPHash, KIND, kCorners, 8>(args, shader, local, nb, smem, agg);
+        dedup_unit<kFrameNT, kPHash, KIND, kCorners, 8, false>(args, shader, local, nb, smem, agg);
     } else if (MODE == kFrameBallot) {
         const uint32_t w = threadIdx.x / kWave;
         const uint32_t b = 4 * local + w;
         unsigned char *mine = smem + w * ballot_stride;
-        if (b < nb) ballot_batch<KIND, kCorners>(A, sh, b, nb, mine, agg);
+        if (b < nb) ballot_batch<KIND, kCorners, false>(A, sh, b, nb, mine, agg);
         __syncthreads();
     } else {
         const unsigned long long sum = naive_chunk<KIND>(A, sh, local, (f4 *)smem);
@@ -205,49 +205,42 @@ __global__ __launch_bounds__(kFrameNT) __attribute__((amdgpu_waves_per_eu(OCC ? 
     }
 }
 
-// Per draw (order position d): counters = the sum of its aggregates;
-// dtot[d] = its invocations.  One wavefront per draw, 16 per workgroup.
+// Per draw (order position d): counters = the sum of its aggregates; the
+// frame's invocations are added to *total_inv (when not NULL), one atomic per
+// workgroup.  One wavefront per draw, 16 per workgroup.
 __global__ __launch_bounds__(1024) void k_frame_finish(const DrawDesc *draws, const uint32_t *order, uint32_t n,
                                                        const uint32_t *slot_base, const unsigned long long *agg,
-                                                       unsigned long long *dtot) {
-    const uint32_t d = blockIdx.x * 16 + threadIdx.x / kWave;
-    if (d >= n) return;
+                                                       unsigned long long *total_inv) {
+    __shared__ unsigned long long part[16];
+    const uint32_t w = threadIdx.x / kWave, d = blockIdx.x * 16 + w;
     unsigned long long sum = 0;
-    const uint32_t i1 = slot_base[d + 1];
-    for (uint32_t i = slot_base[d] + lane_id(); i < i1; i += 4 * kWave) {   // four loads in flight
-        unsigned long long v[4];
+    if (d < n) {
+        const uint32_t i1 = slot_base[d + 1];
+        for (uint32_t i = slot_base[d] + lane_id(); i < i1; i += 4 * kWave) {   // four loads in flight
+            unsigned long long v[4];
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) v[j] = i + j * kWave < i1 ? agg[i + j * kWave] : 0ull;
-        sum += v[0] + v[1] + v[2] + v[3];
+            for (uint32_t j = 0; j < 4; ++j) v[j] = i + j * kWave < i1 ? agg[i + j * kWave] : 0ull;
+            sum += v[0] + v[1] + v[2] + v[3];
+        }
+#pragma unroll
+        for (int s = 32; s > 0; s >>= 1) sum += __shfl_xor(sum, s, kWave);
     }
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) sum += __shfl_xor(sum, s, kWave);
     if (lane_id() == 0) {
         const unsigned long long inv = sum & 0xFFFFFFFFull, units = sum >> 32;
-        unsigned long long *c = draws[order[d]].A.counters;
+        unsigned long long *c = d < n ? draws[order[d]].A.counters : nullptr;
         if (c) {
             c[0] = inv;
             c[1] = units;
             c[2] = 0;
             c[3] = 0;
         }
-        dtot[d] = inv;
+        part[w] = inv;
     }
-}
-
-__global__ __launch_bounds__(1024) void k_frame_total(const unsigned long long *dtot, uint32_t n,
-                                                      unsigned long long *total_inv) {
-    __shared__ unsigned long long part[16];
-    unsigned long long sum = 0;
-    for (uint32_t d = threadIdx.x; d < n; d += 1024) sum += dtot[d];
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) sum += __shfl_xor(sum, s, kWave);
-    if (lane_id() == 0) part[threadIdx.x / kWave] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && total_inv) {
         unsigned long long t = 0;
-        for (int w = 0; w < 16; ++w) t += part[w];
-        *total_inv += t;
+        for (int i = 0; i < 16; ++i) t += part[i];
+        atomicAdd(total_inv, t);
     }
 }
 

@@ -39,6 +39,9 @@ struct CtxWords {
     uint32_t plan_fail;   // epoch of the last planning call whose aligned chain failed
     unsigned long long total_inv;
     unsigned long long pad[6];
+    // words of draws of few batches, taken in turn, so that draws that overlap
+    // on different streams have words of their own
+    unsigned long long arrivals[64];
     unsigned long long spread[kSpread][kSpreadWords];   // streams' part of the total (word 0 of each row)
 
     unsigned long long invocations() const {
@@ -69,6 +72,7 @@ struct vr_ctx {
     Scratch ring;                 // a destroyed stream's buffers, for the next one (at most kRingKept bytes)
     uint32_t host_err = 0;   // data error found on the host, reported by vr_sync
     uint32_t plan_epoch = 0;  // numbers planning calls (0 is never used)
+    uint32_t draw_turn = 0;   // the next draw's word in CtxWords::arrivals
     bool timing = false;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_pool;   // reused event pairs
     size_t ev_used = 0;
@@ -324,7 +328,10 @@ bool dedup_occupancy_bound(const vr_ctx *c, int mode, uint32_t nt, uint32_t lds,
 
 template <int MODE, int KIND>
 void dispatch_nt(vr_ctx *c, uint32_t nt, const DrawArgs &A, const vr_shader_params &sh, uint32_t lds, uint64_t units) {
-    const bool occ = dedup_occupancy_bound(c, MODE, nt, lds, A.plan ? A.max_uniq : A.max_idx, !corners_only(A));
+    // few batches neither fill the chip nor leave registers for the bound
+    // (with batch_done in the bound kernels they spill: plan and hash draw of
+    // the icosphere 120 -> 123 us)
+    const bool occ = !A.arrivals && dedup_occupancy_bound(c, MODE, nt, lds, A.plan ? A.max_uniq : A.max_idx, !corners_only(A));
     switch (nt) {
     case 64: launch_dedup<64, MODE, KIND, false>(c, A, sh, lds, units); break;
     case 128:
@@ -546,7 +553,7 @@ struct vr_frame {
     DrawDesc *d_draws = nullptr;
     vr_shader_params *d_shaders = nullptr;
     uint32_t *d_order = nullptr, *d_unit_base = nullptr, *d_slot_base = nullptr;
-    unsigned long long *d_agg = nullptr, *d_dtot = nullptr;
+    unsigned long long *d_agg = nullptr;
     std::vector<vr::FrameVariant> variants;
     bool index_error = false;
     hipGraph_t graph = nullptr;
@@ -564,7 +571,7 @@ struct FrameLaunch {
     uint32_t n;
     const vr_shader_params *shaders;
     uint32_t *unit_base, *slot_base;
-    unsigned long long *agg, *dtot;
+    unsigned long long *agg;
     const FrameVariant *variants;
     uint32_t num_variants;
     uint32_t *err;
@@ -630,16 +637,13 @@ void enqueue_frame_kernels(const FrameLaunch &L, hipStream_t s) {
                        L.err);
     for (uint32_t i = 0; i < L.num_variants; ++i) frame_variant_dispatch(&L, L.variants[i], s, true);
     hipLaunchKernelGGL(k_frame_finish, dim3((L.n + 15) / 16), dim3(1024), 0, s, L.draws, L.order, L.n,
-                       (const uint32_t *)L.slot_base, (const unsigned long long *)L.agg, L.dtot);
-    if (L.total_inv)
-        hipLaunchKernelGGL(k_frame_total, dim3(1), dim3(1024), 0, s, (const unsigned long long *)L.dtot, L.n,
-                           L.total_inv);
+                       (const uint32_t *)L.slot_base, (const unsigned long long *)L.agg, L.total_inv);
 }
 
 void frame_enqueue(vr_frame *f, hipStream_t s) {
     vr_ctx *c = f->c;
     FrameLaunch L{f->d_draws, f->d_order, f->n, f->d_shaders, f->d_unit_base, f->d_slot_base, f->d_agg,
-                  f->d_dtot, f->variants.data(), (uint32_t)f->variants.size(), &c->d_words->err,
+                  f->variants.data(), (uint32_t)f->variants.size(), &c->d_words->err,
                   &c->d_words->total_inv};
     enqueue_frame_kernels(L, s);
 }
@@ -1047,6 +1051,8 @@ vr_status draw_impl(vr_ctx *c, const uint32_t *d_indices, uint64_t num_indices, 
             A.status_cap = (uint32_t)nb_bound;
         }
     }
+    const bool few = !setup && nb_bound <= kFewBatches;
+    if (few) A.arrivals = &c->d_words->arrivals[c->draw_turn++ % 64];
     TimedRegion timed(c, !noalloc);
     if (is_ballot(strategy)) {
         const uint32_t lds = align16(ballot_lds_bytes(batch_tris));   // per wavefront
@@ -1059,7 +1065,7 @@ vr_status draw_impl(vr_ctx *c, const uint32_t *d_indices, uint64_t num_indices, 
         else dispatch_kind<kPHash>(c, sh.kind, r.nt, A, sh, lds, nb_bound);
     }
     timed.done();
-    if (setup) {   // the units added to the totals themselves
+    if (setup || few) {   // the units added to the totals themselves
         VR_HIP(c, hipGetLastError());
         return VR_OK;
     }
@@ -1322,7 +1328,7 @@ vr_status vr_frame_create(vr_ctx *c, const vr_draw *draws, uint32_t n, const vr_
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t o_draws = 0, o_sh = al(sizeof(DrawDesc) * n), o_ord = o_sh + al(sizeof(vr_shader_params) * ns),
                  o_ub = o_ord + al(4ull * n), o_sb = o_ub + al(4ull * (n + 1)), o_agg = o_sb + al(4ull * (n + 1)),
-                 o_dt = o_agg + al(8 * (slots + 1)), total = o_dt + al(8ull * (n + 1));
+                 total = o_agg + al(8 * (slots + 1));
     if (hipMalloc(&f->mem, total) != hipSuccess) {
         delete f;
         return fail(c, VR_ERR_OOM, "frame allocation of %zu bytes failed", total);
@@ -1334,7 +1340,6 @@ vr_status vr_frame_create(vr_ctx *c, const vr_draw *draws, uint32_t n, const vr_
     f->d_unit_base = (uint32_t *)(m + o_ub);
     f->d_slot_base = (uint32_t *)(m + o_sb);
     f->d_agg = (unsigned long long *)(m + o_agg);
-    f->d_dtot = (unsigned long long *)(m + o_dt);
     hipError_t e = hipSuccess;
     if (n) e = hipMemcpy(f->d_draws, desc.data(), sizeof(DrawDesc) * n, hipMemcpyHostToDevice);
     if (e == hipSuccess && n) e = hipMemcpy(f->d_shaders, shaders, sizeof(vr_shader_params) * ns, hipMemcpyHostToDevice);
@@ -1554,9 +1559,9 @@ struct ServerReq {
 
 // Byte offsets of a tick's staging for n draws.  The head [0, cnt) is
 // uploaded (draw table, shader table, zeroed words), [words, end) is read
-// back (error word and per-draw counters); bases and totals follow.
+// back (error word and per-draw counters); the bases follow.
 struct TickLayout {
-    size_t sh, ord, words, cnt, end, ubase, sbase, dtot, total;
+    size_t sh, ord, words, cnt, end, ubase, sbase, total;
     explicit TickLayout(uint32_t n) {
         auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
         sh = al(sizeof(DrawDesc) * n);
@@ -1566,8 +1571,7 @@ struct TickLayout {
         end = cnt + al(32ull * n);
         ubase = end;
         sbase = ubase + al(4ull * (n + 1));
-        dtot = sbase + al(4ull * (n + 1));
-        total = dtot + al(8ull * n);
+        total = sbase + al(4ull * (n + 1));
     }
 };
 
@@ -1701,7 +1705,7 @@ vr_status server_launch(vr_server *s, uint32_t tick, const std::vector<uint64_t>
     }
     FrameLaunch F{(const DrawDesc *)S.dev, (const uint32_t *)(S.dev + L.ord), n,
                   (const vr_shader_params *)(S.dev + L.sh), (uint32_t *)(S.dev + L.ubase),
-                  (uint32_t *)(S.dev + L.sbase), S.agg, (unsigned long long *)(S.dev + L.dtot), vars.data(),
+                  (uint32_t *)(S.dev + L.sbase), S.agg, vars.data(),
                   (uint32_t)vars.size(), &dw->err, &dw->total_inv};
     S.n = n;
     hipError_t e = hipMemcpyAsync(S.dev, S.host, L.cnt, hipMemcpyHostToDevice, s->stream);
