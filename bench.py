@@ -34,8 +34,8 @@ METRIC = "triangles/s & shading rate per strategy vs no-reuse; p50/p99 draw late
 
 # main kernel of each draw in the step (Phong shading instantiation; the
 # step's dedup units fit the LDS of the occupancy-bound kernels, which they take)
-KERNEL_NAMES = {"naive": "k_naive<1>", "static_ballot": "k_ballot<1>", "dyn_sort": "k_dedup<256, 0, 1, true>",
-                "dyn_hash": "k_dedup<256, 1, 1, true>", "dyn_phash": "k_dedup<256, 2, 1, true>"}
+KERNEL_NAMES = {"naive": "k_naive<1>", "static_ballot": "k_ballot<1, 0>", "dyn_sort": "k_dedup<256, 0, 1, true, 0>",
+                "dyn_hash": "k_dedup<256, 1, 1, true, 0>", "dyn_phash": "k_dedup<256, 2, 1, true, 0>"}
 
 
 def shader_flops(sp):
