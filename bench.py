@@ -597,8 +597,8 @@ def walk_benchmark(stage, steps=10, batch=512):
 def stream_benchmark(stage, idx, vtx, sp, T, chunk=65536, reps=5):
     """The bench mesh streamed in 64K-triangle chunks with static ballot
     rounds (no analysis of the index buffer) through a ring of 1, 2 or 4
-    corner buffers, triangle setup (1920 x 1080) consuming each buffer on a
-    second HIP stream; against the whole mesh as one chunk.  Host wall time
+    corner buffers, triangle setup (1920 x 1080) run by the draws; against the
+    whole mesh as one chunk.  Host wall time
     from the first push to both stages finished."""
     import torch
     from paper_1805_08893_amd import vr
