@@ -599,7 +599,7 @@ def stream_benchmark(stage, idx, vtx, sp, T, chunk=65536, reps=5):
     rounds (no analysis of the index buffer) through a ring of 1, 2 or 4
     corner buffers, triangle setup (1920 x 1080) run by the draws; against the
     whole mesh as one chunk.  Host wall time
-    from the first push to both stages finished."""
+    from the first push until the stream is done."""
     import torch
     from paper_1805_08893_amd import vr
     rec = torch.empty((T, 8), dtype=torch.float32, device="cuda")
