@@ -39,9 +39,6 @@ struct CtxWords {
     uint32_t plan_fail;   // epoch of the last planning call whose aligned chain failed
     unsigned long long total_inv;
     unsigned long long pad[6];
-    // words of draws of few batches, taken in turn, so that draws that overlap
-    // on different streams have words of their own
-    unsigned long long arrivals[64];
     unsigned long long spread[kSpread][kSpreadWords];   // streams' part of the total (word 0 of each row)
 
     unsigned long long invocations() const {
@@ -49,6 +46,16 @@ struct CtxWords {
         for (const auto &row : spread) t += row[0];
         return t;
     }
+};
+
+// What a context keeps on the device.  vr_sync and vr_autotune read, clear and
+// restore the first part alone: they wait for the current stream only, and a
+// draw on another one may be between its first arrival and its last.
+struct CtxMem {
+    CtxWords words;
+    // words of draws of few batches, taken in turn, so that draws that overlap
+    // on different streams have words of their own
+    unsigned long long arrivals[64];
 };
 
 struct Scratch {
@@ -65,6 +72,7 @@ struct vr_ctx {
     size_t lds_limit = 65536;
     std::string error;
     CtxWords *d_words = nullptr;
+    unsigned long long *d_arrivals = nullptr;   // CtxMem::arrivals, in the allocation of d_words
     Scratch status, agg, plan, plan_work, tune, shaded;   // shaded: MULTI's vertex pass
     Scratch plan_status;                                   // the planner's epoch-tagged look-back words
     Scratch selftest;                                      // vr_math_selftest's counter
@@ -72,7 +80,7 @@ struct vr_ctx {
     Scratch ring;                 // a destroyed stream's buffers, for the next one (at most kRingKept bytes)
     uint32_t host_err = 0;   // data error found on the host, reported by vr_sync
     uint32_t plan_epoch = 0;  // numbers planning calls (0 is never used)
-    uint32_t draw_turn = 0;   // the next draw's word in CtxWords::arrivals
+    uint32_t draw_turn = 0;   // the next draw's word in d_arrivals
     bool timing = false;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_pool;   // reused event pairs
     size_t ev_used = 0;
@@ -820,12 +828,14 @@ vr_status vr_create(vr_ctx **out, int device, void *hip_stream) {
         c->num_cus = prop.multiProcessorCount;
         c->lds_limit = prop.sharedMemPerBlock;
     }
-    if (hipMalloc((void **)&c->d_words, sizeof(CtxWords)) != hipSuccess ||
-        hipMemset(c->d_words, 0, sizeof(CtxWords)) != hipSuccess) {
-        if (c->d_words) (void)hipFree(c->d_words);
+    CtxMem *mem = nullptr;
+    if (hipMalloc((void **)&mem, sizeof(CtxMem)) != hipSuccess || hipMemset(mem, 0, sizeof(CtxMem)) != hipSuccess) {
+        if (mem) (void)hipFree(mem);
         delete c;
         return fail(nullptr, VR_ERR_OOM, "context allocation failed");
     }
+    c->d_words = &mem->words;
+    c->d_arrivals = mem->arrivals;
     scratch_setup(device);   // a failure is reported by vr_process_draw_noalloc
     *out = c;
     return VR_OK;
@@ -1052,7 +1062,7 @@ vr_status draw_impl(vr_ctx *c, const uint32_t *d_indices, uint64_t num_indices, 
         }
     }
     const bool few = !setup && nb_bound <= kFewBatches;
-    if (few) A.arrivals = &c->d_words->arrivals[c->draw_turn++ % 64];
+    if (few) A.arrivals = &c->d_arrivals[c->draw_turn++ % 64];
     TimedRegion timed(c, !noalloc);
     if (is_ballot(strategy)) {
         const uint32_t lds = align16(ballot_lds_bytes(batch_tris));   // per wavefront
