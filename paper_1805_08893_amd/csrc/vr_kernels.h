@@ -70,12 +70,12 @@ __device__ __forceinline__ uint32_t launch_units(const DrawArgs &A, uint32_t nb)
         raise_error(A.err, VR_ERR_CAPACITY);
         return A.status_cap;
     }
-    if (A.arrivals && nb > 4095) {   // more than batch_done counts: only with a foreign plan
-        raise_error(A.err, VR_ERR_CAPACITY);
-        return 4095;
-    }
     return nb;
 }
+
+// Batches that count: those within the draw's bound, all of which a launch
+// covers.  A plan built for other limits, or for a longer stream, may list more.
+__device__ __forceinline__ uint32_t counted_batches(const DrawArgs &A, uint32_t nb) { return min(nb, A.status_cap); }
 
 __device__ __forceinline__ uint32_t batch_count(const DrawArgs &A) {
     return A.plan ? A.plan[0] : A.num_batches;
@@ -247,17 +247,19 @@ __global__ __launch_bounds__(256) void k_finish(const uint32_t *plan, uint32_t n
     }
 }
 
-// A draw of at most kFewBatches batches needs no k_finish: every batch adds
-// (1 << 52 | units << 32 | invocations) to one word of the draw (zero between
-// draws), and the batch that finds all others there writes the counters and
-// clears the word and the look-back words.  The sums travel in the word, so
-// nothing else has to be ordered.  A launch costs about 4 us, an addition to
+// A draw of at most kFewBatches batches needs no k_finish: every batch that
+// counts adds (1 << 52 | units << 32 | invocations) to one word of the draw
+// (zero between draws), and the batch that finds all others there writes the
+// counters and clears the word and the look-back words.  The sums travel in the
+// word, so nothing else has to be ordered.  A launch costs about 4 us, an addition to
 // one address about 20 ns: at 128 batches the additions cost at most 2.6 us,
 // and mostly while other batches run (7,938 triangles, plan and hash draw: 22.4
 // -> 20 us; 3,000 triangles, hash 9.8 -> 7.7 us, ballot 13.8 -> 7.3 us).
 constexpr uint32_t kFewBatches = 128;
 
-__device__ __forceinline__ void batch_done(const DrawArgs &A, uint32_t nb, uint32_t units, uint32_t inv) {
+__device__ __forceinline__ void batch_done(const DrawArgs &A, uint32_t b, uint32_t units, uint32_t inv) {
+    const uint32_t nb = counted_batches(A, batch_count(A));
+    if (b >= nb) return;
     const unsigned long long mine = 1ull << 52 | (unsigned long long)units << 32 | inv;
     const unsigned long long all = atomicAdd(A.arrivals, mine) + mine;
     if ((uint32_t)(all >> 52) != nb) return;
@@ -273,9 +275,11 @@ __device__ __forceinline__ void batch_done(const DrawArgs &A, uint32_t nb, uint3
         for (uint32_t i = 0; i < nb; ++i) A.status[i] = 0;
 }
 
-// The draw's first kernel clears its counters before k_finish adds to them.
+// The draw's first kernel clears its counters before k_finish adds to them, or
+// where no batch will write them (an empty plan).
 __device__ __forceinline__ void clear_counters(const DrawArgs &A) {
-    if (blockIdx.x == 0 && threadIdx.x < 4 && A.counters && !A.arrivals) A.counters[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 4 && A.counters && (!A.arrivals || batch_count(A) == 0))
+        A.counters[threadIdx.x] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -999,7 +1003,7 @@ __device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint3
         // read again here, so that nothing is kept for it; a frame's units come
         // with their place
         const DrawArgs &F = *(const DrawArgs *)reread(args);
-        if (FEW && F.arrivals) batch_done(F, launch_units(F, batch_count(F)), 1, inv);
+        if (FEW && F.arrivals) batch_done(F, u, 1, inv);
         else (agg ? agg : F.agg)[u] = (1ull << 32) | inv;
     }
     __syncthreads();   // the caller may reuse the LDS for the next unit
@@ -1215,7 +1219,7 @@ __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_
     }
     if (OUT == kAll && A.unit_offsets && b + 1 == nb && lane == 0) A.unit_offsets[ubase + r] = A.T;
     if (lane == 0) {
-        if (FEW && A.arrivals) batch_done(A, nb, r, inv);
+        if (FEW && A.arrivals) batch_done(A, b, r, inv);
         else agg_out[b] = ((unsigned long long)r << 32) | inv;
     }
 }
@@ -1229,12 +1233,12 @@ template <int KIND, int OUT>
 __global__ __launch_bounds__(kBallotWaves * 64) void k_ballot(DrawArgs A, vr_shader_params sh, uint32_t stride) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     clear_counters(A);
-    uint32_t nb = launch_units(A, batch_count(A));
-    if (A.arrivals) nb = min(nb, A.status_cap);   // the batches the launch covers
+    const uint32_t nb = launch_units(A, batch_count(A));
     const uint32_t w = threadIdx.x / kWave;
     // in dispatch order where batches wait for their predecessors; a dynamic
-    // launch has more workgroups than there are batches
-    const uint32_t pieces = (nb + kBallotWaves - 1) / kBallotWaves;
+    // launch has more workgroups than there are batches, or fewer (a plan built
+    // for other limits)
+    const uint32_t pieces = min((nb + kBallotWaves - 1) / kBallotWaves, gridDim.x);
     if (blockIdx.x >= pieces) return;
     const uint32_t b = (A.need_prefix ? blockIdx.x : xcd_piece(blockIdx.x, pieces)) * kBallotWaves + w;
     if (b >= nb) return;   // only wavefront-level synchronisation follows
