@@ -1004,7 +1004,7 @@ __device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint3
         // with their place
         const DrawArgs &F = *(const DrawArgs *)reread(args);
         if (FEW && F.arrivals) batch_done(F, u, 1, inv);
-        else (agg ? agg : F.agg)[u] = (1ull << 32) | inv;
+        else if (u < F.status_cap) (agg ? agg : F.agg)[u] = (1ull << 32) | inv;   // no room past the bound
     }
     __syncthreads();   // the caller may reuse the LDS for the next unit
 }
@@ -1220,7 +1220,7 @@ __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_
     if (OUT == kAll && A.unit_offsets && b + 1 == nb && lane == 0) A.unit_offsets[ubase + r] = A.T;
     if (lane == 0) {
         if (FEW && A.arrivals) batch_done(A, b, r, inv);
-        else agg_out[b] = ((unsigned long long)r << 32) | inv;
+        else if (b < A.status_cap) agg_out[b] = ((unsigned long long)r << 32) | inv;   // no room past the bound
     }
 }
 

@@ -62,3 +62,34 @@ def test_counters_and_later_draws(name, bt, nu, T, planned, budgets, bound, whol
         assert r["counters"].cpu().tolist() == [*ora["counters"][:2].tolist(), 0, 0]
     assert stage.sync()[0] == vr.VR_OK
     stage.close()
+
+
+def test_batches_past_the_bound_leave_no_trace():
+    """More batches than the allocation-free draw's array holds: every triangle
+    is drawn, the batches within the bound are counted, and the look-back words
+    behind the array's aggregates are as they were."""
+    from paper_1805_08893_amd import vr
+    T = 524288 + 1000   # the array holds 524,288 batches
+    m = W.grid_mesh(513, 520, 4, "scan")
+    sp = W.shader_for_mesh(m, W.SHADER_MVP, 4)
+    idx, vtx = torch.from_numpy(m.indices[:3 * T].view(np.int32)).cuda(), torch.from_numpy(m.vertices).cuda()
+    plan = torch.cat([torch.tensor([T]), torch.arange(T + 1)]).to(torch.int32).cuda()
+    stage = vr.GeometryStage(0)
+    bound = T // 85 + 1
+    print(f"case T={T} bound {bound}", flush=True)
+    naive = stage.draw(idx, vtx, sp, vr.VR_NAIVE, 1, corners=True)
+    res = stage.alloc_outputs(T, vr.VR_DYN_HASH, 341, corners=True)
+    opts = vr.make_opts(max_unique=256, plan=plan)
+    assert vr.vr_process_draw_noalloc(stage.ctx, idx, vtx, sp, vr.VR_DYN_HASH, 341, opts, stage.describe(res)) == vr.VR_OK
+    assert stage.sync()[0] == vr.VR_OK
+    assert res["counters"].cpu().tolist() == [3 * bound, bound, 0, 0]
+    assert torch.equal(res["corners"].view(torch.int32), naive["corners"].view(torch.int32))
+    n = 3000
+    rc, ora = vro.process_draw(m.indices[:3 * n], m.vertices, sp, vro.STATIC_HASH, 1)
+    assert rc == vro.OK
+    res = stage.alloc_outputs(n, vr.VR_STATIC_HASH, 1, corners=True, tris=True, verts=True, units=True)
+    assert vr.vr_process_draw_noalloc(stage.ctx, idx[:3 * n], vtx, sp, vr.VR_STATIC_HASH, 1, None, stage.describe(res)) == vr.VR_OK
+    assert stage.sync()[0] == vr.VR_OK
+    np.testing.assert_array_equal(res["tris"].cpu().numpy().view(np.uint32), ora["tris"])
+    np.testing.assert_array_equal(res["unit_invocations"].cpu().numpy().view(np.uint32)[:n], ora["unit_invocations"])
+    stage.close()
