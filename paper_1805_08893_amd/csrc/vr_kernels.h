@@ -251,16 +251,28 @@ __global__ __launch_bounds__(256) void k_finish(const uint32_t *plan, uint32_t n
 // counts adds (1 << 52 | units << 32 | invocations) to one word of the draw
 // (zero between draws), and the batch that finds all others there writes the
 // counters and clears the word and the look-back words.  The sums travel in the
-// word, so nothing else has to be ordered.  A launch costs about 4 us, an addition to
-// one address about 20 ns: at 128 batches the additions cost at most 2.6 us,
-// and mostly while other batches run (7,938 triangles, plan and hash draw: 22.4
-// -> 20 us; 3,000 triangles, hash 9.8 -> 7.7 us, ballot 13.8 -> 7.3 us).
-constexpr uint32_t kFewBatches = 128;
+// word and need no order with other memory.  The look-back words do: a batch's
+// arrival is a release after its last store to them and its last load of
+// others', and the batch that clears them acquires every arrival first, so that
+// no earlier store can follow the zeros.
+//
+// A launch costs about 4 us, an addition to one address about 20 ns: at 128
+// batches the additions cost at most 2.6 us, and mostly while other batches run
+// (7,938 triangles, plan and hash draw: 22.4 -> 21.3 us; 3,000 triangles, hash
+// 9.8 -> 7.7 us, ballot 13.8 -> 7.3 us).  A release writes back its XCD's L2 and
+// waits: with look-back words k_finish is as quick from about 32 batches on
+// (indexed outputs, k_finish and arrivals: 25 batches 12.4 and 11.5 us, 94 10.7
+// and 13.3 us, 125 12.4 and 14.8 us).
+constexpr uint32_t kFewBatches = 128, kFewPrefixed = 32;   // without look-back words, with them
 
+// PREFIX: the draw may have look-back words.
+template <bool PREFIX>
 __device__ __forceinline__ void batch_done(const DrawArgs &A, uint32_t b, uint32_t units, uint32_t inv) {
     const uint32_t nb = counted_batches(A, batch_count(A));
     if (b >= nb) return;
     const unsigned long long mine = 1ull << 52 | (unsigned long long)units << 32 | inv;
+    const bool prefix = PREFIX && A.need_prefix;
+    if (prefix) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     const unsigned long long all = atomicAdd(A.arrivals, mine) + mine;
     if ((uint32_t)(all >> 52) != nb) return;
     atomicExch(A.arrivals, 0ull);
@@ -271,8 +283,10 @@ __device__ __forceinline__ void batch_done(const DrawArgs &A, uint32_t b, uint32
         A.counters[3] = 0;
     }
     atomicAdd(A.total_inv, all & 0xFFFFFFFFull);
-    if (A.need_prefix)
-        for (uint32_t i = 0; i < nb; ++i) A.status[i] = 0;
+    if (prefix) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        for (uint32_t i = 0; i < nb; ++i) status_store(&A.status[i], 0);
+    }
 }
 
 // The draw's first kernel clears its counters before k_finish adds to them, or
@@ -1003,7 +1017,7 @@ __device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint3
         // read again here, so that nothing is kept for it; a frame's units come
         // with their place
         const DrawArgs &F = *(const DrawArgs *)reread(args);
-        if (FEW && F.arrivals) batch_done(F, u, 1, inv);
+        if (FEW && F.arrivals) batch_done<FULL>(F, u, 1, inv);
         else if (u < F.status_cap) (agg ? agg : F.agg)[u] = (1ull << 32) | inv;   // no room past the bound
     }
     __syncthreads();   // the caller may reuse the LDS for the next unit
@@ -1219,7 +1233,7 @@ __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_
     }
     if (OUT == kAll && A.unit_offsets && b + 1 == nb && lane == 0) A.unit_offsets[ubase + r] = A.T;
     if (lane == 0) {
-        if (FEW && A.arrivals) batch_done(A, b, r, inv);
+        if (FEW && A.arrivals) batch_done<OUT == kAll>(A, b, r, inv);
         else if (b < A.status_cap) agg_out[b] = ((unsigned long long)r << 32) | inv;   // no room past the bound
     }
 }

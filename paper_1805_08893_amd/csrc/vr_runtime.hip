@@ -419,7 +419,7 @@ std::map<int, ScratchSlot> g_scratch;
 
 // With `device` current: looks up the array's address on it and zeroes its
 // look-back words (a fill kernel, waited for), once per device.  Every draw
-// that uses look-back words clears the ones it used in its k_finish, so they
+// that uses look-back words clears the ones it used (batch_done or k_finish), so they
 // are zero again at the start of the next call.
 void scratch_setup(int device) {
     std::lock_guard<std::mutex> lk(g_scratch_mu);
@@ -1061,7 +1061,7 @@ vr_status draw_impl(vr_ctx *c, const uint32_t *d_indices, uint64_t num_indices, 
             A.status_cap = (uint32_t)nb_bound;
         }
     }
-    const bool few = !setup && nb_bound <= kFewBatches;
+    const bool few = !setup && nb_bound <= (A.need_prefix ? kFewPrefixed : kFewBatches);
     if (few) A.arrivals = &c->d_arrivals[c->draw_turn++ % 64];
     TimedRegion timed(c, !noalloc);
     if (is_ballot(strategy)) {
