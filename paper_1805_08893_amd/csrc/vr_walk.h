@@ -7,6 +7,7 @@
 #pragma once
 
 #include "vr_device.h"
+#include "vr_walk_pieces.h"
 
 namespace vr {
 
@@ -292,11 +293,6 @@ __global__ __launch_bounds__(256) void k_walk_naive(WalkArgs W) {
     }
 }
 
-// A window of the activity field staged in LDS: up to kWalkSide x kWalkSide
-// cells in rows of kWalkPitch words (odd, so that a column spreads over the
-// LDS banks).
-constexpr int32_t kWalkSide = 64, kWalkPitch = 65;
-
 // One batch of up to kWalkMaxBatch agents per workgroup of NT threads: the
 // batch's cells go into an LDS hash table (linear probing, 2 x kWalkMaxBatch
 // slots); the lane that inserts a cell takes the next id; each distinct cell
@@ -402,17 +398,9 @@ __global__ __launch_bounds__(NT) void k_walk_hash(WalkArgs W) {
     const uint32_t bx = s_box[0], by = s_box[1], outside = s_nsel;
     const bool any = bx <= s_box[2];
     const uint32_t bw = any ? s_box[2] - bx + 1 : 0u, bh = any ? s_box[3] - by + 1 : 0u;
-    // pieces a side: as few as fit the window, and as many as there are workgroups
-    uint32_t split = W.parts >= 16 ? 4u : W.parts >= 4 ? 2u : 1u;
-    const uint32_t room = 2 * R < kWalkSide ? (uint32_t)(kWalkSide - 2 * R) : 0u;   // cells a side besides the margins
-    bool windowed = LISTED && room > 0;
-    if (windowed) {
-        while ((bw + split - 1) / split > room || (bh + split - 1) / split > room) ++split;
-        // a piece costs a few barriers and a window whatever its cells; short
-        // searches over many pieces are quicker from memory (49 moves, 100,000
-        // agents on 200 x 200 cells: 31.7 us in pieces, 17.8 us without)
-        windowed = 16 * split * split <= W.num_moves;
-    }
+    const WalkPieces pieces = walk_pieces(bw, bh, (uint32_t)R, W.parts, W.num_moves);
+    const uint32_t split = pieces.split;
+    const bool windowed = LISTED && pieces.windowed;
     const uint32_t pw = max(1u, (bw + split - 1) / split), ph = max(1u, (bh + split - 1) / split);
     uint32_t evaluated = outside;
     for (uint32_t piece = part; any && piece < (windowed ? split * split : W.parts); piece += W.parts) {
