@@ -253,11 +253,13 @@ vr_status vr_process_draw_noalloc(vr_ctx *ctx, const uint32_t *d_indices, uint64
  * w <= 0 gives an all-zero record).  Records land in d_records (caller-owned,
  * float[records_cap][8] = {xmin, ymin, xmax, ymax, area, flags, 0, 0}, flags
  * a uint32 with bit 0 = visible) at the triangle's position in the stream.
- * The buffers are drawn into in turn, in the order of the context's stream,
- * so memory stays bounded for any stream length; a destroyed stream leaves up
- * to 256 MB of them to the context for the next one.  Static batches restart
- * at every chunk.  A stream belongs to its context and must be
- * destroyed before it; push is not thread safe.  Errors: VR_ERR_ARG (slots outside 1..8,
+ * The buffers are drawn into in turn, so memory stays bounded for any stream
+ * length; a destroyed stream leaves up to 256 MB of them to the context for
+ * the next one.  Static batches restart at every chunk.  The context may move
+ * to another HIP stream between pushes (vr_set_stream): later chunks follow
+ * the earlier ones, except under a capture, which waits for nothing outside.
+ * A stream belongs to its context and must be destroyed before it; push is not
+ * thread safe.  Errors: VR_ERR_ARG (slots outside 1..8,
  * chunk_tris outside 1..2^24, a dynamic strategy, a chunk above chunk_tris),
  * VR_ERR_CAPACITY (records_cap exceeded), draw errors as vr_process_draw.
  */

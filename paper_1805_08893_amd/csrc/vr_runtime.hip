@@ -76,7 +76,7 @@ struct vr_ctx {
     Scratch status, agg, plan, plan_work, tune, shaded;   // shaded: MULTI's vertex pass
     Scratch plan_status;                                   // the planner's epoch-tagged look-back words
     Scratch selftest;                                      // vr_math_selftest's counter
-    int live_streams = 0;         // vr_stream objects
+    std::vector<vr_stream *> streams;   // the context's vr_stream objects
     Scratch ring;                 // a destroyed stream's buffers, for the next one (at most kRingKept bytes)
     uint32_t host_err = 0;   // data error found on the host, reported by vr_sync
     uint32_t plan_epoch = 0;  // numbers planning calls (0 is never used)
@@ -554,6 +554,73 @@ vr_status build_plan(vr_ctx *c, const uint32_t *d_idx, uint32_t T, uint32_t V, u
 
 }  // namespace
 
+// Streams: chunks drawn into a ring of corner slots; each draw's kernel runs
+// triangle setup on its units (vr_stream.h).  Chunks write records of their own
+// and add to the totals atomically, and no one reads a slot, so chunks on
+// different HIP streams need no order among them; the totals' clearing comes
+// before all of them, and finish waits for all.
+struct vr_stream {
+    vr_ctx *c = nullptr;
+    uint32_t slots = 0, chunk_tris = 0, width = 0, height = 0;
+    f4 *records = nullptr;
+    uint64_t records_cap = 0;
+    Scratch mem;                              // the slots, then the totals
+    size_t slot_bytes = 0;
+    unsigned long long *totals = nullptr;     // [kSpread][kSpreadWords]
+    uint64_t pushed = 0, next = 0;
+    hipEvent_t left = nullptr;   // recorded on the HIP stream the context left, behind this stream's work there
+    bool here = false;           // work on the context's HIP stream
+    bool behind = false;         // `left` stands for work on another one
+    bool lost = false;           // work elsewhere that no event could be recorded behind
+};
+
+namespace {
+
+// Whether a HIP stream takes part in a capture, or cannot be asked while one is
+// running: then no event is recorded on it and it is made to wait for none,
+// which would invalidate the capture or draw other streams into it.
+bool in_capture(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(s, &st) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    return !known || st != hipStreamCaptureStatusNone;
+}
+
+// The context leaves its HIP stream: the stream's work there gets an event behind it.
+void stream_leave(vr_stream *s, hipStream_t from) {
+    if (!s->here) return;
+    s->here = false;
+    if (!in_capture(from) && hipEventRecord(s->left, from) == hipSuccess) {
+        s->behind = true;
+    } else {
+        (void)hipGetLastError();
+        s->lost = true;
+    }
+}
+
+// New work of the stream on the context's HIP stream follows the work it left.
+vr_status stream_arrive(vr_stream *s) {
+    vr_ctx *c = s->c;
+    if (s->behind && !in_capture(c->stream)) {
+        VR_HIP(c, hipStreamWaitEvent(c->stream, s->left, 0));
+        s->behind = false;
+    }
+    s->here = true;
+    return VR_OK;
+}
+
+// Waits for the stream's work, wherever it is.
+vr_status stream_wait(vr_stream *s) {
+    vr_ctx *c = s->c;
+    if (s->lost) VR_HIP(c, hipDeviceSynchronize());
+    if (s->behind) VR_HIP(c, hipEventSynchronize(s->left));
+    VR_HIP(c, hipStreamSynchronize(c->stream));
+    s->here = s->behind = s->lost = false;
+    return VR_OK;
+}
+
+}  // namespace
+
 struct vr_frame {
     vr_ctx *c = nullptr;
     uint32_t n = 0;
@@ -859,14 +926,9 @@ void vr_destroy(vr_ctx *c) {
 vr_status vr_set_stream(vr_ctx *c, void *hip_stream) {
     if (!c) return VR_ERR_ARG;
     const hipStream_t to = (hipStream_t)hip_stream;
-    if (c->live_streams && to != c->stream) {   // the chunks a stream pushed so far precede its next ones
+    if (to != c->stream && !c->streams.empty()) {
         DeviceGuard g(c->device);
-        hipEvent_t e = nullptr;
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess) {
-            if (hipEventRecord(e, c->stream) == hipSuccess) (void)hipStreamWaitEvent(to, e, 0);
-            (void)hipEventDestroy(e);
-        }
-        (void)hipGetLastError();   // a stream that is gone has nothing to wait for
+        for (vr_stream *s : c->streams) stream_leave(s, c->stream);
     }
     c->stream = to;
     return VR_OK;
@@ -1105,22 +1167,6 @@ vr_status vr_process_draw_noalloc(vr_ctx *c, const uint32_t *d_indices, uint64_t
                      true);
 }
 
-// ---------------------------------------------------------------------------
-// Streams: chunks drawn into a ring of corner slots; each draw's kernel runs
-// triangle setup on its units (vr_stream.h), and the context's stream orders
-// the reuse of a slot.
-// ---------------------------------------------------------------------------
-struct vr_stream {
-    vr_ctx *c = nullptr;
-    uint32_t slots = 0, chunk_tris = 0, width = 0, height = 0;
-    f4 *records = nullptr;
-    uint64_t records_cap = 0;
-    Scratch mem;                              // the slots, then the totals
-    size_t slot_bytes = 0;
-    unsigned long long *totals = nullptr;     // [kSpread][kSpreadWords]
-    uint64_t pushed = 0, next = 0;
-};
-
 namespace {
 constexpr size_t kTotalsBytes = sizeof(unsigned long long) * kSpread * kSpreadWords;
 constexpr size_t kRingKept = 256u << 20;
@@ -1157,13 +1203,20 @@ vr_status vr_stream_create(vr_ctx *c, uint32_t slots, uint32_t chunk_tris, uint3
     s->mem = mem;
     s->slot_bytes = slot_bytes;
     s->totals = (unsigned long long *)((unsigned char *)mem.ptr + slot_bytes * slots);
-    hipLaunchKernelGGL(k_fill_u64, dim3(2), dim3(256), 0, c->stream, s->totals, (uint64_t)kSpread * kSpreadWords, 0ull);
-    if (hipGetLastError() != hipSuccess) {
+    hipError_t e = hipEventCreateWithFlags(&s->left, hipEventDisableTiming);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_fill_u64, dim3(2), dim3(256), 0, c->stream, s->totals, (uint64_t)kSpread * kSpreadWords,
+                           0ull);
+        e = hipGetLastError();
+    }
+    if (e != hipSuccess) {
+        if (s->left) (void)hipEventDestroy(s->left);
         (void)hipFree(mem.ptr);
         delete s;
-        return fail(c, VR_ERR_DEVICE, "stream: clearing the totals");
+        return fail(c, VR_ERR_DEVICE, "stream setup: %s", hipGetErrorString(e));
     }
-    ++c->live_streams;
+    s->here = true;
+    c->streams.push_back(s);
     *out = s;
     return VR_OK;
 }
@@ -1186,8 +1239,11 @@ vr_status vr_stream_push(vr_stream *s, const uint32_t *d_indices, uint64_t num_i
     vr_outputs out{};
     out.corners = (float *)((unsigned char *)s->mem.ptr + s->next % s->slots * s->slot_bytes);
     const SetupTarget setup{s->records + 2 * s->pushed, s->width, s->height, s->totals, c->d_words->spread[0]};
-    vr_status st = draw_impl(c, d_indices, num_indices, d_vertices, num_vertices, shader, strategy, batch_tris, nullptr,
-                             &out, false, &setup);
+    DeviceGuard g(c->device);
+    vr_status st = stream_arrive(s);
+    if (st != VR_OK) return st;
+    st = draw_impl(c, d_indices, num_indices, d_vertices, num_vertices, shader, strategy, batch_tris, nullptr, &out,
+                   false, &setup);
     if (st != VR_OK) return st;
     ++s->next;
     s->pushed += T;
@@ -1199,7 +1255,8 @@ vr_status vr_stream_finish(vr_stream *s, uint64_t *h_triangles, uint64_t *h_visi
     vr_ctx *c = s->c;
     DeviceGuard g(c->device);
     unsigned long long t[kSpread][kSpreadWords];
-    VR_HIP(c, hipStreamSynchronize(c->stream));
+    const vr_status st = stream_wait(s);
+    if (st != VR_OK) return st;
     VR_HIP(c, hipMemcpy(t, s->totals, sizeof t, hipMemcpyDeviceToHost));
     unsigned long long visible = 0, inv = 0;
     for (const auto &row : t) {
@@ -1216,8 +1273,9 @@ void vr_stream_destroy(vr_stream *s) {
     if (!s) return;
     vr_ctx *c = s->c;
     DeviceGuard g(c->device);
-    (void)hipStreamSynchronize(c->stream);
-    --c->live_streams;
+    (void)stream_wait(s);
+    (void)hipEventDestroy(s->left);
+    c->streams.erase(std::find(c->streams.begin(), c->streams.end(), s));
     // the context keeps one set of buffers for the next stream
     if (s->mem.bytes <= kRingKept && s->mem.bytes > c->ring.bytes) std::swap(s->mem, c->ring);
     if (s->mem.ptr) (void)hipFree(s->mem.ptr);
