@@ -477,10 +477,14 @@ __host__ __device__ inline DedupLds dedup_lds_layout(int mode, bool dynamic, uin
         L.stab = d;  d += 3u * 256u * sort_groups(m, nt);
     }
     off = max(align16(off + 48 * sv_rows), align16(d));
-    L.tmp = off;  off += 64;   // scan words, or counts (uint8) per row and wavefront
+    L.tmp = off;  off += 64;   // scan words, or counts (uint8) per row and wavefront; then three words of the unit
     L.total = off;
     return L;
 }
+
+// LDS a dedup kernel takes besides that layout: with 1,024 threads the scan
+// fills its words, and those of the unit are static.
+__host__ __device__ constexpr uint32_t dedup_lds_static(uint32_t nt) { return nt < 1024 ? 0u : 12u; }
 
 // Bytes a unit counts for against the device's LDS limit: the sizes a call
 // may ask for follow from this (never less than the layout above takes), so
@@ -705,7 +709,10 @@ __device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint3
     uint32_t *s_table = (uint32_t *)(smem + L.table);
     uint32_t *s_first = (uint32_t *)(smem + L.first);
     uint32_t *s_tmp = (uint32_t *)(smem + L.tmp);
-    __shared__ uint32_t s_vbase, s_count, s_min, s_max;
+    __shared__ uint32_t s_static[NT < 1024 ? 1 : dedup_lds_static(NT) / 4];
+    uint32_t *s_unit = NT < 1024 ? s_tmp + 12 : s_static;
+    uint32_t &s_count = s_unit[0], &s_min = s_unit[1], &s_max = s_unit[2];
+    uint32_t &s_vbase = s_unit[0];   // known after the last use of the count
 
     const uint32_t tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid / kWave);
     uint32_t t0, t1;

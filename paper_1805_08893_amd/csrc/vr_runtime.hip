@@ -989,17 +989,30 @@ vr_status draw_impl(vr_ctx *c, const uint32_t *d_indices, uint64_t num_indices, 
     uint32_t lds = 0;
     bool stream = false;
     if (strategy != VR_NAIVE && strategy != VR_MULTI && !is_ballot(strategy)) {
-        lds = dedup_lds_layout(mode, is_dynamic(strategy), r.max_idx, r.max_uniq, r.hash_bits, r.nt, r.max_uniq).total;
         uint32_t counted = dedup_lds_counted(mode, r.max_idx, r.max_uniq, r.size_bits, r.size_nt, r.max_uniq);
         if (!out->corners && 3 * counted > c->lds_limit)
             counted = dedup_lds_counted(mode, r.max_idx, r.max_uniq, r.size_bits, r.size_nt, r.size_nt);
         // indexed outputs only: shaded vertices stream out when keeping them all
         // would leave room for fewer than three workgroups per CU
-        if (!out->corners && 3 * lds > c->lds_limit) {
-            stream = true;
-            lds = dedup_lds_layout(mode, is_dynamic(strategy), r.max_idx, r.max_uniq, r.hash_bits, r.nt, r.nt).total;
+        auto fit = [&]() {
+            const bool dyn = is_dynamic(strategy);
+            lds = dedup_lds_layout(mode, dyn, r.max_idx, r.max_uniq, r.hash_bits, r.nt, r.max_uniq).total;
+            stream = !out->corners && 3 * lds > c->lds_limit;
+            if (stream) lds = dedup_lds_layout(mode, dyn, r.max_idx, r.max_uniq, r.hash_bits, r.nt, r.nt).total;
+            return lds + dedup_lds_static(r.nt) <= c->lds_limit;
+        };
+        // what the counted size allows is accepted: with the threads it was counted
+        // with, and a dynamic sort's table gives way, down to one slot per index
+        bool fits = fit();
+        if (!fits && r.nt != r.size_nt) {
+            r.nt = r.size_nt;
+            fits = fit();
         }
-        if (std::max(counted, lds) > c->lds_limit)
+        while (!fits && mode == kSort && is_dynamic(strategy) && (1u << r.hash_bits) >= 2 * r.max_uniq) {
+            --r.hash_bits;
+            fits = fit();
+        }
+        if (counted > c->lds_limit || !fits)
             return fail(c, VR_ERR_ARG,
                         "LDS need %u B exceeds the %zu B limit (lower max_unique, batch_tris or hash_slots, or "
                         "request indexed outputs only)",
