@@ -270,8 +270,18 @@ vr_status check_args(vr_ctx *c, uint64_t num_indices, uint32_t num_vertices, con
         // default at least as many threads as hold a whole unit (hash 1024 /
         // 1365, Hilbert order: 30.3 us with 256 threads, 23.6 us with 1024);
         // not fewer than before where the LDS of the worst case limits the
-        // workgroups (static 85: 13.4 us with 64 threads, 11.2 us with 128)
-        if (!o.wg_size) r.nt = std::max(nt, threads(1u << log2u((r.max_idx + kRows - 1) / kRows)));
+        // workgroups (static 85: 13.4 us with 64 threads, 11.2 us with 128).
+        // Where N_pmax is far above what N_u lets a batch hold, a whole unit is
+        // that of a closed mesh (about 2 N_u triangles, 6 N_u corners), or of
+        // N_u * 4 / 3 triangles where units wait for their predecessors and
+        // every surplus workgroup costs its wavefronts (398,000 triangles, 64
+        // / 1024 indexed: 178 us with the 1024 threads of N_pmax, 43 us with
+        // 128; 256 / 1024 in Hilbert and random order, corners: 28.1 and 110
+        // us with 1024, 20.8 and 63.7 us with 512; indexed: 46.0 and 177 us
+        // with 1024, 27.1 and 85.8 us with 512, 31.5 and 59.8 us with 256)
+        const bool prefix = out->tris || out->verts || out->unit_offsets || out->unit_invocations;
+        const uint32_t whole = std::min(r.max_idx, (prefix ? 4u : 6u) * r.max_uniq);
+        if (!o.wg_size) r.nt = std::max(nt, threads(1u << log2u((whole + kRows - 1) / kRows)));
         uint32_t slots = o.hash_slots ? o.hash_slots : std::max<uint32_t>(8, 1u << log2u(2 * r.max_uniq));
         r.size_bits = log2u(slots);
         // twice the slots (at most a third full instead of a half) shorten the
