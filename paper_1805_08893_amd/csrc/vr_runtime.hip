@@ -1344,7 +1344,8 @@ vr_status vr_walk_step(vr_ctx *c, const uint32_t *d_keys_in, uint32_t num_agents
     if (strategy == VR_NAIVE) {
         TimedRegion timed(c);
         const dim3 grid_n((num_agents + 255) / 256);
-        if (list_bytes) hipLaunchKernelGGL(k_walk_naive<true>, grid_n, dim3(256), list_bytes, c->stream, W);
+        if (list_bytes && num_moves >= kWalkNaiveListed)
+            hipLaunchKernelGGL(k_walk_naive<true>, grid_n, dim3(256), list_bytes, c->stream, W);
         else hipLaunchKernelGGL(k_walk_naive<false>, grid_n, dim3(256), 0, c->stream, W);
         VR_HIP(c, hipGetLastError());
         return VR_OK;

@@ -30,6 +30,25 @@ CASES = [(200, 19, (80, 90, 26, 26), 600, 300),     # 64 x 64 cells: the largest
          (40, 60, (3, 5, 20, 9), 20000, 64)]        # 313 batches: one workgroup each
 
 
+@pytest.mark.parametrize("num", [1, 19, 20])
+def test_few_moves_per_agent(num):
+    from paper_1805_08893_amd import vr
+    s = W.walk_setup(5, grid=50, agents=700, radius=5, gaussians=3)
+    s.moves, s.weights = np.ascontiguousarray(s.moves[:num]), np.ascontiguousarray(s.weights[:num])
+    u = W.walk_uniforms(5, 1, 700)
+    rc, ref, _ = vro.walk_step(s.keys, s, u, vro.NAIVE)
+    assert rc == vro.OK
+    stage = vr.GeometryStage(0)
+    kin = _dev(s.keys)
+    kout = torch.empty_like(kin)
+    print(f"case naive, {num} moves", flush=True)
+    assert vr.vr_walk_step(stage.ctx, kin, _dev(s.activity), 50, _dev(s.moves), _dev(s.weights), _dev(u), vr.VR_NAIVE, 0,
+                           kout) == vr.VR_OK
+    assert stage.sync()[0] == vr.VR_OK
+    np.testing.assert_array_equal(kout.cpu().numpy().view(np.uint32), ref)
+    stage.close()
+
+
 @pytest.mark.parametrize("grid,radius,box,agents,batch", CASES)
 @pytest.mark.parametrize("strategy", ["hash", "naive"])
 def test_tiles(grid, radius, box, agents, batch, strategy):
