@@ -72,6 +72,7 @@ struct NextClass {
     static constexpr uint32_t per = (corners + threads - 1) / threads;
     static constexpr uint32_t bits = ceil_log2(corners + corners / 8);
     static constexpr uint32_t slots = 1u << bits;
+    static constexpr uint32_t near = TMC == 4096 ? 3 : 1;   // see probe_next
     // LDS: keys -> links to another corner of the same index (+ the difference
     // arrays), the hash table -> the first corner of each slot's list, previous
     // occurrences packed per triangle (three 16-bit positions in 64 bits)
@@ -95,12 +96,18 @@ struct CheckClass {
 };
 
 // A key's place in a table of 2^bits slots (bits <= 18) is the upper bits of
-// its hash; the next one is an odd distance, taken from the lower bits, away:
-// keys that meet in one slot part again, where linear probing would join them
-// to a cluster.  A wavefront goes on until the last of its keys is placed, so
-// the longest chain counts (random windows fill half of k_plan_next's table).
-// Its windows of ordered meshes repeat their indices and are indifferent; so
-// is the sparser table of k_plan_check, which probes linearly.
+// its hash.  The next one or three (NextClass::near) are the slots behind it, and
+// from then on an odd distance, taken from the lower bits, each time: a wavefront
+// goes on until the last of its keys is placed, so the longest chain counts.
+// Indices of an ordered mesh that share a place also share most lower bits and
+// would follow each other along the same distant slots; next to it there is room,
+// as they fill a sixth of the table (1,341 x 789 vertices in Hilbert order, window
+// of 4,608 triangles: up to 36 probes with distances at once, 2 so).  Random
+// windows fill half of it or more and make clusters, which distances leave (up to
+// 146 probes by neighbours alone, 35 so), but each near probe adds to them.
+// 4096 / 2048, 126,000 triangles in Hilbert order: 130 us with distances at once,
+// 91 us so; 341 / 256, 8.4M in random order: 317, 319 and 326 us with no, one and
+// three near probes.
 __device__ __forceinline__ uint32_t probe_next(uint32_t h, uint32_t bits) {
     return h + (((h >> 3 & 0x7Eu) | 1u) << (32u - bits));
 }
@@ -256,16 +263,19 @@ __attribute__((amdgpu_waves_per_eu(TMC <= 512 ? 8 : 1))) void k_plan_next(PlanAr
     if (bad) raise_error(P.err, VR_ERR_INDEX_RANGE);
     __syncthreads();
     // insertion in lockstep rounds, so that the LDS round trips overlap
-    while (pending) {
+    auto insert = [&](auto next) {
 #pragma unroll
         for (uint32_t k = 0; k < kPer; ++k) {
             if (pending & (1ull << k)) {
                 const uint32_t prev = atomicCAS(&s_tab[slot[k] >> (32 - kBits)], kEmpty, key[k]);
                 if (prev == kEmpty || prev == key[k]) pending &= ~(1ull << k);
-                else slot[k] = probe_next(slot[k], kBits);
+                else slot[k] = next(slot[k]);
             }
         }
-    }
+    };
+    for (uint32_t round = 0; pending && round < Win::near; ++round)
+        insert([](uint32_t h) { return h + (1u << (32 - kBits)); });
+    while (pending) insert([](uint32_t h) { return probe_next(h, kBits); });
 #pragma unroll
     for (uint32_t k = 0; k < kPer; ++k) slot[k] >>= 32 - kBits;
     // the corners of each slot as a list: a slot's word becomes its head, every
