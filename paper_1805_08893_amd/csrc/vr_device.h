@@ -260,21 +260,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *tmp, u
     return before + incl - v;
 }
 
-// Workgroup-wide min / max (contain barriers: call uniformly).
-template <int NT>
-__device__ __forceinline__ uint32_t block_reduce_min(uint32_t v, uint32_t *tmp) {
-    constexpr int NW = NT / kWave;
-    v = wave_min(v);
-    __syncthreads();
-    if (lane_id() == 0) tmp[threadIdx.x / kWave] = v;
-    __syncthreads();
-    uint32_t r = tmp[0];
-#pragma unroll
-    for (int i = 1; i < NW; ++i) r = min(r, tmp[i]);
-    __syncthreads();
-    return r;
-}
-
+// Workgroup-wide max (contains barriers: call uniformly).
 template <int NT>
 __device__ __forceinline__ uint32_t block_reduce_max(uint32_t v, uint32_t *tmp) {
     constexpr int NW = NT / kWave;

@@ -371,7 +371,7 @@ __global__ __launch_bounds__(256) void k_naive_records(DrawArgs A, vr_shader_par
             vis = setup_triangle(A.setup, c, t0 + tid);
         }
         const uint32_t seen = (uint32_t)__popcll(ballot(vis));
-        if (lane_id() == 0) setup_totals(A.setup, 2 * blockIdx.x + tid / kWave, seen, tid == 0 ? 3 * ntri : 0u, ntri);
+        if (lane_id() == 0) setup_totals(A.setup, 2 * blockIdx.x + tid / kWave, seen, tid == 0 ? 3 * ntri : 0u);
     }
 }
 
@@ -1025,7 +1025,7 @@ __device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint3
         write_unit<NT, OUT>(B, t0, t1 - t0, s_local, s_sv, inv, FULL ? s_vbase : 0u, u, at, stream);
     if (OUT == kRecords) {
         const uint32_t seen = fits && inv > 0 ? setup_unit<NT>(B.setup, t0, t1 - t0, s_local, s_sv, at) : 0u;
-        if (lane == 0) setup_totals(B.setup, u * NW + w, seen, at == 0 ? inv : 0u, 1);
+        if (lane == 0) setup_totals(B.setup, u * NW + w, seen, at == 0 ? inv : 0u);
     } else if (at == 0) {
         // read again here, so that nothing is kept for it; a frame's units come
         // with their place
@@ -1241,7 +1241,7 @@ __device__ __forceinline__ void ballot_batch(const DrawArgs &A, const vr_shader_
         cur = end;
     }
     if (OUT == kRecords) {
-        if (lane == 0) setup_totals(A.setup, b, seen, inv, r);
+        if (lane == 0) setup_totals(A.setup, b, seen, inv);
         return;
     }
     if (OUT == kAll && A.unit_offsets && b + 1 == nb && lane == 0) A.unit_offsets[ubase + r] = A.T;

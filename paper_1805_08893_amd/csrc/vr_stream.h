@@ -22,7 +22,7 @@ constexpr uint32_t kSpread = 64, kSpreadWords = 8;
 struct SetupTarget {
     f4 *records;                        // of the chunk's first triangle
     uint32_t width, height;
-    unsigned long long *totals;         // [kSpread][kSpreadWords]: visible, invocations, units
+    unsigned long long *totals;         // [kSpread][kSpreadWords]: visible, invocations
     unsigned long long *invocations;    // [kSpread][kSpreadWords]: the context's
 };
 
@@ -74,13 +74,11 @@ __device__ __forceinline__ uint32_t setup_unit(const SetupTarget &S, uint32_t t0
 }
 
 // Adds to the totals of workgroup (or wavefront) `who`; called by one lane.
-__device__ __forceinline__ void setup_totals(const SetupTarget &S, uint32_t who, uint32_t visible, uint32_t inv,
-                                             uint32_t units) {
+__device__ __forceinline__ void setup_totals(const SetupTarget &S, uint32_t who, uint32_t visible, uint32_t inv) {
     const uint32_t row = who % kSpread * kSpreadWords;
     if (visible) atomicAdd(&S.totals[row], (unsigned long long)visible);
     if (inv) {
         atomicAdd(&S.totals[row + 1], (unsigned long long)inv);
-        atomicAdd(&S.totals[row + 2], (unsigned long long)units);
         atomicAdd(&S.invocations[row], (unsigned long long)inv);
     }
 }
