@@ -11,13 +11,16 @@ shaded output and the invocation count:
     hash and parallel hash (256 / 341).
 value = triangles processed per second over the whole step (all strategies,
 inputs resident in HBM).  Per-strategy throughput and shading rate are
-reported beside it, with the roofline of the dominant kernel and the CPU
-oracle timed on a bounded sample.
+reported beside it, with the roofline of the dominant kernel, in one JSON
+line on stdout.  The other legs (the CPU oracle timed on a bounded sample,
+indexed outputs, sweeps, streaming, the walk, scenes, serving) follow the
+progress messages on stderr, one JSON line each.
 """
 import argparse
 import glob
 import hashlib
 import json
+import math
 import os
 import sys
 import time
@@ -778,6 +781,27 @@ def serving_benchmark(stage, seed=11, n=2000, rate=500.0, budget=64 << 30, small
             "budget_256MB": small}
 
 
+# What the one line on stdout holds; every other leg goes to stderr, a line each,
+# so that the line stays short enough to be kept whole by whoever reads it.
+HEADLINE = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+            "vs_baseline", "dtype", "data", "config", "roofline", "per_strategy")
+
+
+def significant(x, digits=6):
+    """x with every float rounded to so many significant digits."""
+    if isinstance(x, dict):
+        return {k: significant(v, digits) for k, v in x.items()}
+    if isinstance(x, (list, tuple)):
+        return [significant(v, digits) for v in x]
+    return float(f"{x:.{digits}g}") if isinstance(x, float) and math.isfinite(x) else x
+
+
+def headline(line):
+    """The line on stdout: the contract's fields as measured, the rest rounded."""
+    exact = ("value", "ms_per_step")
+    return json.dumps({k: line[k] if k in exact else significant(line[k]) for k in HEADLINE})
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -1025,7 +1049,9 @@ def main():
             "roofline": roof, "cpu_baseline": cpu, "per_strategy": per, "indexed": indexed, "sweep": sweep_rows,
             "multi": multi, "cold": cold, "plain": plain, "heavy": heavy, "stream": stream, "walk": walk, "scene": scene,
             "serving": serving}
-    print(json.dumps(line), flush=True)
+    for key in sorted(set(line) - set(HEADLINE)):
+        print(json.dumps({key: significant(line[key])}), file=sys.stderr, flush=True)
+    print(headline(line), flush=True)
     stage.close()
 
 
