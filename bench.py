@@ -11,9 +11,9 @@ shaded output and the invocation count:
     hash and parallel hash (256 / 341).
 value = triangles processed per second over the whole step (all strategies,
 inputs resident in HBM).  Per-strategy throughput and shading rate are
-reported beside it, with the roofline of the dominant kernel, in one JSON
-line on stdout.  The other legs (the CPU oracle timed on a bounded sample,
-indexed outputs, sweeps, streaming, the walk, scenes, serving) follow the
+reported beside it, with the roofline of the dominant kernel and the CPU
+oracle timed on a bounded sample, in one JSON line on stdout.  The other legs
+(indexed outputs, sweeps, streaming, the walk, scenes, serving) follow the
 progress messages on stderr, one JSON line each.
 """
 import argparse
@@ -784,7 +784,7 @@ def serving_benchmark(stage, seed=11, n=2000, rate=500.0, budget=64 << 30, small
 # What the one line on stdout holds; every other leg goes to stderr, a line each,
 # so that the line stays short enough to be kept whole by whoever reads it.
 HEADLINE = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
-            "vs_baseline", "dtype", "data", "config", "roofline", "per_strategy")
+            "vs_baseline", "dtype", "data", "config", "roofline", "cpu_baseline", "per_strategy")
 
 
 def significant(x, digits=6):
