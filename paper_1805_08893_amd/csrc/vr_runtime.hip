@@ -78,6 +78,7 @@ struct vr_ctx {
     Scratch selftest;                                      // vr_math_selftest's counter
     std::vector<vr_stream *> streams;   // the context's vr_stream objects
     Scratch ring;                 // a destroyed stream's buffers, for the next one (at most kRingKept bytes)
+    bool ring_idle = false;       // untouched since the last vr_sync: the next one gives it back
     uint32_t host_err = 0;   // data error found on the host, reported by vr_sync
     uint32_t plan_epoch = 0;  // numbers planning calls (0 is never used)
     uint32_t draw_turn = 0;   // the next draw's word in d_arrivals
@@ -1211,6 +1212,7 @@ vr_status vr_stream_create(vr_ctx *c, uint32_t slots, uint32_t chunk_tris, uint3
     if (c->ring.bytes >= bytes) {   // the buffers a destroyed stream left; its work precedes this one's
         mem = c->ring;
         c->ring = Scratch();
+        c->ring_idle = false;
     } else {
         if (hipMalloc(&mem.ptr, bytes) != hipSuccess) return fail(c, VR_ERR_OOM, "stream slots: out of memory");
         mem.bytes = bytes;
@@ -1300,7 +1302,10 @@ void vr_stream_destroy(vr_stream *s) {
     (void)hipEventDestroy(s->left);
     c->streams.erase(std::find(c->streams.begin(), c->streams.end(), s));
     // the context keeps one set of buffers for the next stream
-    if (s->mem.bytes <= kRingKept && s->mem.bytes > c->ring.bytes) std::swap(s->mem, c->ring);
+    if (s->mem.bytes <= kRingKept && s->mem.bytes > c->ring.bytes) {
+        std::swap(s->mem, c->ring);
+        c->ring_idle = false;
+    }
     if (s->mem.ptr) (void)hipFree(s->mem.ptr);
     delete s;
 }
@@ -1381,6 +1386,11 @@ vr_status vr_sync(vr_ctx *c, uint64_t *h_invocations) {
     CtxWords w{};
     VR_HIP(c, hipMemcpy(&w, c->d_words, sizeof w, hipMemcpyDeviceToHost));
     VR_HIP(c, hipMemset(c->d_words, 0, sizeof w));
+    if (c->ring.ptr && c->ring_idle) {
+        VR_HIP(c, hipFree(c->ring.ptr));
+        c->ring = Scratch();
+    }
+    c->ring_idle = true;
     if (h_invocations) *h_invocations = w.invocations();
     uint32_t e = c->host_err ? c->host_err : w.err;
     c->host_err = 0;
