@@ -482,9 +482,11 @@ __host__ __device__ inline DedupLds dedup_lds_layout(int mode, bool dynamic, uin
     return L;
 }
 
-// LDS a dedup kernel takes besides that layout: with 1,024 threads the scan
-// fills its words, and those of the unit are static.
-__host__ __device__ constexpr uint32_t dedup_lds_static(uint32_t nt) { return nt < 1024 ? 0u : 12u; }
+// LDS a dedup kernel takes besides that layout, which starts at the next 16 bytes:
+// a word of the unit at a fixed address up to 256 threads (with it in the layout
+// a frame's hashing variants take 0.5 % longer), and with 1,024 threads, whose
+// scan fills the layout's words, all three.
+__host__ __device__ constexpr uint32_t dedup_lds_static(uint32_t nt) { return nt <= 256 || nt == 1024 ? 16u : 0u; }
 
 // Bytes a unit counts for against the device's LDS limit: the sizes a call
 // may ask for follow from this (never less than the layout above takes), so
@@ -709,10 +711,11 @@ __device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint3
     uint32_t *s_table = (uint32_t *)(smem + L.table);
     uint32_t *s_first = (uint32_t *)(smem + L.first);
     uint32_t *s_tmp = (uint32_t *)(smem + L.tmp);
-    __shared__ uint32_t s_static[NT < 1024 ? 1 : dedup_lds_static(NT) / 4];
+    __shared__ __attribute__((aligned(16))) uint32_t s_static[NT == 512 ? 1 : dedup_lds_static(NT) / 4];
     uint32_t *s_unit = NT < 1024 ? s_tmp + 12 : s_static;
-    uint32_t &s_count = s_unit[0], &s_min = s_unit[1], &s_max = s_unit[2];
-    uint32_t &s_vbase = s_unit[0];   // known after the last use of the count
+    uint32_t &s_min = s_unit[1], &s_max = s_unit[2];
+    uint32_t &s_count = NT == 512 ? s_unit[0] : s_static[0];
+    uint32_t &s_vbase = s_count;   // known after the last use of the count
 
     const uint32_t tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid / kWave);
     uint32_t t0, t1;

@@ -579,7 +579,7 @@ struct vr_stream {
     size_t slot_bytes = 0;
     unsigned long long *totals = nullptr;     // [kSpread][kSpreadWords]
     uint64_t pushed = 0, next = 0;
-    hipEvent_t left = nullptr;   // recorded on the HIP stream the context left, behind this stream's work there
+    hipEvent_t left = nullptr;   // recorded on a HIP stream the context left, behind this stream's work there
     bool here = false;           // work on the context's HIP stream
     bool behind = false;         // `left` stands for work on another one
     bool lost = false;           // work elsewhere that no event could be recorded behind
@@ -601,7 +601,9 @@ bool in_capture(hipStream_t s) {
 void stream_leave(vr_stream *s, hipStream_t from) {
     if (!s->here) return;
     s->here = false;
-    if (!in_capture(from) && hipEventRecord(s->left, from) == hipSuccess) {
+    if (!in_capture(from) &&
+        (s->left || hipEventCreateWithFlags(&s->left, hipEventDisableTiming) == hipSuccess) &&
+        hipEventRecord(s->left, from) == hipSuccess) {
         s->behind = true;
     } else {
         (void)hipGetLastError();
@@ -861,9 +863,10 @@ vr_status frame_variants(vr_ctx *c, const DrawDesc *desc, const FrameNeeds *need
         v.ballot_stride = need.ballot_stride;
         v.unit_lds = align16(std::max(need.unit_lds, 4 * need.ballot_stride));
         v.lds_total = need.lds_total(hi - lo);
-        if (need.lds_counted(hi - lo) > c->lds_limit)
-            return fail(c, VR_ERR_ARG, "frame variant needs %u B of LDS per workgroup (limit %zu)",
-                        need.lds_counted(hi - lo), c->lds_limit);
+        const uint32_t counted = need.lds_counted(hi - lo) + (v.mode <= kFramePHash ? dedup_lds_static(kFrameNT) : 0u);
+        if (counted > c->lds_limit)
+            return fail(c, VR_ERR_ARG, "frame variant needs %u B of LDS per workgroup (limit %zu)", counted,
+                        c->lds_limit);
         // hashing variants take the occupancy-bound kernel when eight
         // workgroups (eight wavefronts per SIMD) fit in the LDS
         v.occ = (v.mode == kFrameHash || v.mode == kFramePHash) && 8ull * (v.lds_total + 64u) <= c->lds_limit;
@@ -1228,17 +1231,11 @@ vr_status vr_stream_create(vr_ctx *c, uint32_t slots, uint32_t chunk_tris, uint3
     s->mem = mem;
     s->slot_bytes = slot_bytes;
     s->totals = (unsigned long long *)((unsigned char *)mem.ptr + slot_bytes * slots);
-    hipError_t e = hipEventCreateWithFlags(&s->left, hipEventDisableTiming);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_fill_u64, dim3(2), dim3(256), 0, c->stream, s->totals, (uint64_t)kSpread * kSpreadWords,
-                           0ull);
-        e = hipGetLastError();
-    }
-    if (e != hipSuccess) {
-        if (s->left) (void)hipEventDestroy(s->left);
+    hipLaunchKernelGGL(k_fill_u64, dim3(2), dim3(256), 0, c->stream, s->totals, (uint64_t)kSpread * kSpreadWords, 0ull);
+    if (hipGetLastError() != hipSuccess) {
         (void)hipFree(mem.ptr);
         delete s;
-        return fail(c, VR_ERR_DEVICE, "stream setup: %s", hipGetErrorString(e));
+        return fail(c, VR_ERR_DEVICE, "stream: clearing the totals");
     }
     s->here = true;
     c->streams.push_back(s);
@@ -1299,7 +1296,7 @@ void vr_stream_destroy(vr_stream *s) {
     vr_ctx *c = s->c;
     DeviceGuard g(c->device);
     (void)stream_wait(s);
-    (void)hipEventDestroy(s->left);
+    if (s->left) (void)hipEventDestroy(s->left);
     c->streams.erase(std::find(c->streams.begin(), c->streams.end(), s));
     // the context keeps one set of buffers for the next stream
     if (s->mem.bytes <= kRingKept && s->mem.bytes > c->ring.bytes) {
@@ -2059,7 +2056,7 @@ static vr_status server_submit_locked(vr_server *s, const vr_request *r, uint64_
     D.d_corners = (float *)s->arena;
     if (describe_draw(s->ctx, D, r->shader, 0, X, need, nullptr) != VR_OK)
         return server_fail(s, VR_ERR_ARG, "%s", s->ctx->error.c_str());
-    if (need.lds_counted(s->cfg.max_tick_draws) > s->ctx->lds_limit)
+    if (need.lds_counted(s->cfg.max_tick_draws) + dedup_lds_static(kFrameNT) > s->ctx->lds_limit)
         return server_fail(s, VR_ERR_ARG, "the request needs more LDS than a tick allows");
     const uint64_t bytes = 144ull * r->num_tris;
     uint64_t t = 0;
