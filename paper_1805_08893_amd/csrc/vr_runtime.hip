@@ -614,9 +614,12 @@ void stream_leave(vr_stream *s, hipStream_t from) {
 // New work of the stream on the context's HIP stream follows the work it left.
 vr_status stream_arrive(vr_stream *s) {
     vr_ctx *c = s->c;
-    if (s->behind && !in_capture(c->stream)) {
-        VR_HIP(c, hipStreamWaitEvent(c->stream, s->left, 0));
-        s->behind = false;
+    if (s->behind) {
+        DeviceGuard g(c->device);
+        if (!in_capture(c->stream)) {
+            VR_HIP(c, hipStreamWaitEvent(c->stream, s->left, 0));
+            s->behind = false;
+        }
     }
     s->here = true;
     return VR_OK;
@@ -1261,7 +1264,6 @@ vr_status vr_stream_push(vr_stream *s, const uint32_t *d_indices, uint64_t num_i
     vr_outputs out{};
     out.corners = (float *)((unsigned char *)s->mem.ptr + s->next % s->slots * s->slot_bytes);
     const SetupTarget setup{s->records + 2 * s->pushed, s->width, s->height, s->totals, c->d_words->spread[0]};
-    DeviceGuard g(c->device);
     vr_status st = stream_arrive(s);
     if (st != VR_OK) return st;
     st = draw_impl(c, d_indices, num_indices, d_vertices, num_vertices, shader, strategy, batch_tris, nullptr, &out,
