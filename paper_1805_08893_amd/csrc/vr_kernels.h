@@ -692,7 +692,7 @@ __device__ __forceinline__ void insert_rows(const DrawArgs &A, uint32_t *s_table
 // with the indices staged in LDS, one row at a time and every kernel argument
 // kept in (spilled) scalar registers, hash took 1,245 vector instructions per
 // wavefront and 53.3 us, sort 2,220 and 64.0 us, indexed phash 61.2 us; so
-// hash takes 941 and 51.7 us, sort 1,320 and 57.3 us, indexed phash 50.1 us.
+// hash takes 945 and 51.2 us, sort 1,344 and 57.4 us, indexed phash 50.1 us.
 // ---------------------------------------------------------------------------
 template <int NT, int MODE, int KIND, int OUT, uint32_t SORT_ROUNDS, bool FEW>
 __device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint32_t u, uint32_t nb,
@@ -1044,6 +1044,14 @@ __device__ __forceinline__ void dedup_unit(ArgsPtr args, ShaderPtr shader, uint3
 // lane: indexed phash 128 / 128 36.7 us at 8, 35.0 us at 7).
 __host__ __device__ constexpr int dedup_waves(int mode, bool full) { return mode == kSort || full ? 7 : 8; }
 
+// The other kernels: as many as their LDS mostly leaves anyway.  A sort of 64
+// threads with more outputs than corners is given six instead of five (static
+// 32, 398,000 triangles in random order, Phong-9: indexed 73.2 -> 69.9 us, every
+// output 83.7 -> 78.5 us; with corners alone 37.8 -> 45.6 us with MVP).
+__host__ __device__ constexpr int dedup_waves_free(int mode, bool full, int nt) {
+    return mode != kSort || (full && nt == 64) ? 6 : 5;
+}
+
 struct DedupLaunch {
     DrawArgs A;
     vr_shader_params sh;
@@ -1061,7 +1069,7 @@ struct DedupLaunch {
 // more of a unit's serial latency; otherwise the bound would only add
 // spills.
 template <int NT, int MODE, int KIND, bool OCC, int OUT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC ? dedup_waves(MODE, OUT == kAll) : MODE == kSort ? 5 : 6))) void k_dedup(DedupLaunch) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC ? dedup_waves(MODE, OUT == kAll) : dedup_waves_free(MODE, OUT == kAll, NT)))) void k_dedup(DedupLaunch) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // the launch's only argument, at the start of the kernel-argument segment
     const VR_CONSTANT DedupLaunch *P = (const VR_CONSTANT DedupLaunch *)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1118,7 +1126,7 @@ __host__ __device__ inline uint32_t ballot_lds_bytes(uint32_t batch_tris) {
 // instead (broadcast, compare, ballot, about 14 instructions each in one
 // dependent chain) took 1,639 vector and 906 scalar instructions per batch of
 // 64 triangles and 63.7 us for the icosphere's 20,480 batches (Phong-8); the
-// table's few LDS round trips take 1,070 and 581, and 53.3 us.
+// table's few LDS round trips take 1,051 and 577, and 52.8 us.
 constexpr uint32_t kRoundBits = 8, kRoundSlots = 1u << kRoundBits;   // at most 64 + 63 indices at once
 
 __device__ __forceinline__ uint32_t ballot_round(const DrawArgs &A, uint32_t t0, uint32_t cur, uint32_t t1,

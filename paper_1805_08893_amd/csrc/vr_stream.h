@@ -5,7 +5,8 @@
 // {area, flags, 0, 0} as two float4 per triangle.  A chunk is then one launch,
 // and latency, not traffic, bounds a chunk: with a kernel, a reduction and a
 // consumer on a second HIP stream per chunk, ordered by events, 20 chunks of
-// 65,536 triangles (ballot, Phong-8) took 812 us, so 319 us (400 before the rounds of k_ballot got shorter).
+// 65,536 triangles (ballot, Phong-8) took 812 us, so 310 us (400 before the rounds
+// of k_ballot got shorter).
 #pragma once
 
 #include "vr_device.h"
