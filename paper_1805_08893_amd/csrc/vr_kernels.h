@@ -1275,8 +1275,8 @@ __global__ __launch_bounds__(kBallotWaves * 64) void k_ballot(DrawArgs A, vr_sha
     const uint32_t w = threadIdx.x / kWave;
     // in dispatch order where batches wait for their predecessors; a dynamic
     // launch has more workgroups than there are batches, or fewer (a plan built
-    // for other limits)
-    const uint32_t pieces = min((nb + kBallotWaves - 1) / kBallotWaves, gridDim.x);
+    // for other limits: the launch covers the draw's bound)
+    const uint32_t pieces = (min(nb, A.status_cap) + kBallotWaves - 1) / kBallotWaves;
     if (blockIdx.x >= pieces) return;
     const uint32_t b = (A.need_prefix ? blockIdx.x : xcd_piece(blockIdx.x, pieces)) * kBallotWaves + w;
     if (b >= nb) return;   // only wavefront-level synchronisation follows
